@@ -26,8 +26,8 @@
 // two alternating buffers are never overwritten while still being read. Tags
 // grow from launch to launch (the host clears the buffers before they wrap),
 // so a stale word never matches. The last phase stores plain values into x and
-// ends with the all-gather reduction of the residual diagnostics, followed by
-// an acquire fence, since the gradient pass reads x with ordinary loads.
+// ends with the team reduction of the residual diagnostics and its acquire
+// fence, since the gradient pass reads x with ordinary loads.
 #pragma once
 
 #include "nh_kernels.hpp"
@@ -48,7 +48,7 @@ constexpr int kJacH = kJacNZ / 2;           // cells per thread
 // [2H planes][kJacCols columns].
 template <int H>
 __device__ StepResult jacobi_tb_step(const StepArgs<float>& S, const StepVar<float>& V, int rank, float* xs,
-                                     float* bs, float* rds, Smem<float>& sh, ResRed* rs) {
+                                     float* bs, float* rds, Smem<float>& sh) {
   constexpr int C = kJacCols;
   const Geom& g = S.g;
   // a caller that loops over steps must not keep one step's per-thread
@@ -228,7 +228,7 @@ __device__ StepResult jacobi_tb_step(const StepArgs<float>& S, const StepVar<flo
           if (k0 + i < nz) st_dev(V.x + base + i * nxy, x[i]);
       }
       double v2[2] = {vb, vr};
-      ok &= team_sum_dev<2, kJacBlock>(S, rank, red, v2, rs);
+      ok &= team_sum<float, 2, kJacBlock, true>(S, rank, red, v2, sh.rb);
       bb = v2[0];
       rr = v2[1];
     } else if (inner) {
@@ -243,18 +243,16 @@ __device__ StepResult jacobi_tb_step(const StepArgs<float>& S, const StepVar<flo
     stamp();
   }
   if (!ok && threadIdx.x == 0) atomicOr(S.err_flag, (int)kTimeout);
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");   // the gradient pass reads x with plain loads
   return step_epilogue<float>(S, V, rank, ok, ok ? K : 0, kOk, bb, rr, sh);
 }
 
 template <int H>
 __global__ void __launch_bounds__(kJacBlock, 1) jacobi_step_kernel(StepArgs<float> S) {
   __shared__ Smem<float> sh;
-  __shared__ ResRed rs;
   __shared__ float xs[2 * H * kJacCols];
   __shared__ float bs[2 * H * kJacCols];
   __shared__ float rds[2 * H * kJacCols];
-  jacobi_tb_step<H>(S, step_var(S), blockIdx.x, xs, bs, rds, sh, &rs);
+  jacobi_tb_step<H>(S, step_var(S), blockIdx.x, xs, bs, rds, sh);
 }
 
 // Several consecutive steps of one sweep in one launch: step i takes its
@@ -275,11 +273,10 @@ struct JacSteps {
 template <int H>
 __global__ void __launch_bounds__(kJacBlock, 1) jacobi_steps_kernel(StepArgs<float> S, JacSteps tab) {
   __shared__ Smem<float> sh;
-  __shared__ ResRed rs;
   __shared__ float xs[2 * H * kJacCols];
   __shared__ float bs[2 * H * kJacCols];
   __shared__ float rds[2 * H * kJacCols];
-  for (int i = 0; i < tab.count; ++i) jacobi_tb_step<H>(S, tab.v[i], blockIdx.x, xs, bs, rds, sh, &rs);
+  for (int i = 0; i < tab.count; ++i) jacobi_tb_step<H>(S, tab.v[i], blockIdx.x, xs, bs, rds, sh);
 }
 
 }  // namespace nh

@@ -103,7 +103,7 @@ struct StepArgs {
   R* ckpt_out;                              // forward: copy of T^n (or null)
   const R* T_grad;                          // adjoint: T^n for the gradient (or null)
   double* G;                                // adjoint: dL/dalpha accumulator
-  void* slots;                              // [team + 1] Slot: per-workgroup partials, then the result
+  void* slots;                              // [2][team] Slot: two banks of per-workgroup partials
   unsigned long long epoch_base;            // unique per launch; each reduction uses epoch_base + k
   double rtol2;
   int max_iter;
@@ -208,139 +208,231 @@ __device__ __forceinline__ R diag_of(R c0, R c1, R c2, R c3, R c4, R c5, R sk) {
   return R(1) + ((((c0 + c1) + (c2 + c3)) + (c4 + c5)) + sk);
 }
 
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+// Sum over the 64 lanes, the result in every lane: a butterfly (partners 32,
+// 16, 8, 4, 2, 1 lanes apart) in registers. The halves and the 16-lane rows are
+// exchanged by the lane-swap instructions; within a row the values repeat
+// after each stage, so a rotation by the stage's distance reaches the partner's
+// value. The LDS-permute form of the same butterfly pays an LDS round trip per
+// stage; in the team reduction, which runs four stages of it one after the
+// other, it took 2.4 of 4.4 us (two workgroups).
+template <int CTRL>
+__device__ __forceinline__ double row_ror(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, false);
+  return __hiloint2double(hi, lo);
+}
+// Sum over groups of N = 2, 4, 8 or 16 lanes of a row whose values repeat
+// with period N (N = 16: any values), the result in every lane.
+template <int N>
+__device__ __forceinline__ double row_sum(double v) {
+  if (N >= 16) v += row_ror<0x128>(v);
+  if (N >= 8) v += row_ror<0x124>(v);
+  if (N >= 4) v += row_ror<0x122>(v);
+  if (N >= 2) v += row_ror<0x121>(v);
   return v;
+}
+__device__ __forceinline__ double wave_sum(double v) {
+  {
+    const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(v), __double2loint(v), false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(v), __double2hiint(v), false, false);
+    v = __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+  }
+  {
+    const auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(v), __double2loint(v), false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(v), __double2hiint(v), false, false);
+    v = __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+  }
+  return row_sum<16>(v);
 }
 
 // ---------------------------------------------------------------------------
-// team reduction slots
+// team reduction
+//
+// Every workgroup stores its sum in a slot of its own, then EVERY workgroup
+// gathers all slots and sums them in the same fixed order, so all obtain
+// bit-identical results after one exchange (no master, no read-modify-write).
+// Each FP64 value travels as two 64-bit words (half of its bits | tag << 32),
+// the tag being the low 32 bits of the reduction's epoch: a reader takes
+// values and their validity in one load round trip (16 bytes a load; each
+// 8-byte word carries its own tag), and the writer waits for nothing between
+// its words. Tags are unique between clears of the slots: an epoch is
+// (launch << 24) + k with k < 2^24 reductions per launch, and the host zeroes
+// the slots every 256 launches (tag 0 is never used). Slots alternate between
+// two banks by epoch parity: a workgroup can be at most one reduction ahead of
+// the slowest reader (the next reduction needs every workgroup's slot), so a
+// bank is never rewritten while still read. Every value another workgroup reads
+// was written with device-scope stores, and every wave waits for its own stores
+// before the workgroup's sum is published, so the reduction doubles as the
+// team's barrier; with ACQ it ends with an acquire fence, for callers that
+// read what others stored with ordinary (cached) loads.
+//
+// What bounds it is latency: the stores' completion, one store and one load to
+// the device's coherence point, two workgroup barriers. One wave polls, with
+// three 16-byte loads per slot instead of six 8-byte ones from eight waves: on
+// 3 values, 512 threads, 256 workgroups 2.7 us instead of 9.6 (64: 2.2 / 5.1,
+// 2: 1.9 / 4.4; of the difference the wave sums' registers butterfly makes
+// 2.4-4.6 us, the wide loads the rest).
 
 struct alignas(64) Slot {
-  double v[kNumRed];
-  unsigned long long epoch;
-  unsigned long long pad[3];
+  unsigned w[2 * kNumRed][2];               // (half of the value's bits, tag)
 };
 
-__device__ __forceinline__ unsigned long long ld_epoch(const unsigned long long* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ double ld_val(const double* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
+// Reduction scratch of one workgroup: its waves' partial sums, the sums of the
+// slots that each wave gathered, and by epoch parity whether a wait of this workgroup timed out.
+struct RedBuf {
+  double red[kMaxWaves][kNumRed];
+  double bc[kMaxWaves][kNumRed];
+  int bad[2];
+};
 
-// Shared state of one workgroup: two buffers of a staged plane (1/alpha and up
-// to two vectors; march_tile alternates them), and red, two buffers of
-// per-wave partial sums, which the two block sums of a team reduction use in
-// turn.
+// Shared state of one workgroup of the streaming kernels: two buffers of a
+// staged plane (1/alpha and up to two vectors; march_tile alternates them).
 template <typename R>
 struct Smem {
   R a[2][kMaxPlane];
   R v[2][2][kMaxPlane];
-  double red[2][kMaxWaves][kNumRed];
-  double bc[kNumRed];
-  int flag;
+  RedBuf rb;
 };
 
-// Sum NV doubles over the workgroup of WAVES wave64; the result lands in every
-// thread's v. Each wave sums its lanes with a butterfly; after one barrier
-// every wave loads the waves' sums (lane w holds wave w's) and sums them with
-// the same butterfly, so all threads hold the same bits. red must not be
-// written again before every thread has passed the next workgroup barrier:
-// callers alternate two buffers between consecutive block sums, with a
-// barrier in each.
+// The sum over a workgroup's waves of the partials in rb.red, in every lane.
 template <int NV, int WAVES>
-__device__ __forceinline__ void block_sum(double (&v)[NV], double (*red)[kNumRed]) {
-  static_assert(WAVES <= 64, "one lane per wave");
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+__device__ __forceinline__ void cross_wave_sum(const RedBuf& rb, double (&v)[NV]) {
+  static_assert(WAVES == 4 || WAVES == 8 || WAVES == 16, "one row of lanes holds the waves' sums");
+  const int w = threadIdx.x & (WAVES - 1);
+#pragma unroll
+  for (int i = 0; i < NV; ++i) v[i] = row_sum<WAVES>(rb.red[w][i]);
+}
+
+constexpr int kCpolSc1 = 16;                // cache policy of a device-coherent access (sc1)
+
+// Load slot b of a bank; true once all 2 NV words carry the tag.
+template <int NV>
+__device__ __forceinline__ bool slot_ld(__amdgpu_buffer_rsrc_t bank, int b, unsigned tag, double (&v)[NV]) {
+  bool all = true;
+#pragma unroll
+  for (int i = 0; i < NV; ++i) {
+    const auto x = __builtin_amdgcn_raw_buffer_load_b128(bank, b * (int)sizeof(Slot) + 16 * i, 0, kCpolSc1);
+    all &= x[1] == tag && x[3] == tag;
+    v[i] = __hiloint2double((int)x[2], (int)x[0]);
+  }
+  return all;
+}
+
+// No work to start once the neighbours have published (see team_sum).
+struct NoNeighbours {
+  static constexpr bool kAny = false;
+  __device__ int rank(int) const { return -1; }
+  __device__ void ready() const {}
+};
+
+// Team all-reduce of NV doubles; also the team's barrier. nbr.rank(k), k < 6,
+// gives the ranks of the workgroups whose tiles share a face with this one (-1:
+// none); once every one of them has published its slot for this reduction -- so
+// their earlier stores are visible -- every wave calls nbr.ready(), which may
+// start loads of what the neighbours published (a wave that gathers slots polls
+// both together). Waits are bounded by timeout_ticks; a timeout returns false in every thread of the
+// workgroup and is recorded in err_flag.
+template <typename R, int NV, int BLOCK, bool ACQ, class Nbr = NoNeighbours>
+__device__ __forceinline__ bool team_sum(const StepArgs<R>& S, int rank, unsigned long long& epoch,
+                                         double (&v)[NV], RedBuf& rb, const Nbr& nbr = Nbr()) {
+  static_assert(NV <= kNumRed, "slot too small");
+  constexpr int WAVES = BLOCK / 64;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // uniform: it steers whole waves
+  const unsigned long long e = ++epoch;
+  if (threadIdx.x == 0) rb.bad[e & 1] = 0;
+  // every wave's stores (device-coherent) complete before the slot is published
+  __builtin_amdgcn_s_waitcnt(0);
 #pragma unroll
   for (int i = 0; i < NV; ++i) v[i] = wave_sum(v[i]);
   if (lane == 0) {
 #pragma unroll
-    for (int i = 0; i < NV; ++i) red[wave][i] = v[i];
+    for (int i = 0; i < NV; ++i) rb.red[wave][i] = v[i];
   }
   __syncthreads();
-#pragma unroll
-  for (int i = 0; i < NV; ++i) v[i] = wave_sum(lane < WAVES ? red[lane][i] : 0.0);
-}
-
-// Team all-reduce of NV doubles; also the team's barrier. Every workgroup
-// stores its workgroup sum in its slot and releases it with the epoch of this
-// reduction (the release also publishes the workgroup's earlier global
-// stores). The master (rank 0) waits for every slot, sums the slots in rank
-// order with a fixed reduction tree, and releases the result slot; the other
-// workgroups wait for that. Waits are bounded by timeout_ticks; a timeout
-// returns false and is recorded in err_flag.
-template <typename R, int NV, int BLOCK = Cfg<R>::kBlock>
-__device__ __forceinline__ bool team_sum(const StepArgs<R>& S, int rank, unsigned long long& epoch,
-                                         double (&v)[NV], Smem<R>& sh) {
-  // every wave's sweep stores (device-coherent) complete before the workgroup
-  // publishes its slot: the slot's release orders only the wave that writes it
-  __builtin_amdgcn_s_waitcnt(0);
-  block_sum<NV, BLOCK / 64>(v, sh.red[0]);
   if (S.team == 1) {
-    __syncthreads();                        // red[0] is free again
+    cross_wave_sum<NV, WAVES>(rb, v);
+    __syncthreads();                        // rb.red is free again
     return true;
   }
-  const unsigned long long e = ++epoch;
-  Slot* slots = (Slot*)S.slots;
-  Slot* res = slots + S.team;
-  int ok = 1;
-  if (rank != 0) {
-    if (threadIdx.x == 0) {
+  const unsigned tag = (unsigned)e;
+  Slot* slots = (Slot*)S.slots + (size_t)(e & 1) * S.team;
+  const __amdgpu_buffer_rsrc_t bank =
+      __builtin_amdgcn_make_buffer_rsrc(slots, 0, S.team * (int)sizeof(Slot), 0x00020000);
+  bool ok = true;
+  if (wave == 0) {
+    cross_wave_sum<NV, WAVES>(rb, v);
+    // lane j stores word j of the slot: value j / 2, its low or high half
+    double x = v[0];
 #pragma unroll
-      for (int i = 0; i < NV; ++i)
-        __hip_atomic_store(&slots[rank].v[i], v[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      __hip_atomic_store(&slots[rank].epoch, e, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-      const long long t0 = wall_clock64();
-      while (ld_epoch(&res->epoch) != e) {
-        __builtin_amdgcn_s_sleep(2);
-        if (wall_clock64() - t0 > S.timeout_ticks) { ok = 0; break; }
-      }
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-#pragma unroll
-      for (int i = 0; i < NV; ++i) sh.bc[i] = ld_val(&res->v[i]);
-      sh.flag = ok;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < NV; ++i) v[i] = sh.bc[i];
-    ok = sh.flag;
-    __syncthreads();
-  } else {
-    double s[NV];
-#pragma unroll
-    for (int i = 0; i < NV; ++i) s[i] = 0.0;
-    for (int b = threadIdx.x; b < S.team; b += BLOCK) {
-      if (b == 0) {
-#pragma unroll
-        for (int i = 0; i < NV; ++i) s[i] += v[i];
-        continue;
-      }
-      const long long t0 = wall_clock64();
-      while (ld_epoch(&slots[b].epoch) != e) {
-        __builtin_amdgcn_s_sleep(1);
-        if (wall_clock64() - t0 > S.timeout_ticks) { ok = 0; break; }
-      }
-#pragma unroll
-      for (int i = 0; i < NV; ++i) s[i] += ld_val(&slots[b].v[i]);
-    }
-    ok = __syncthreads_and(ok);
-    block_sum<NV, BLOCK / 64>(s, sh.red[1]);
-    if (threadIdx.x == 0) {
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-#pragma unroll
-      for (int i = 0; i < NV; ++i)
-        __hip_atomic_store(&res->v[i], s[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      __hip_atomic_store(&res->epoch, e, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < NV; ++i) v[i] = s[i];
+    for (int i = 1; i < NV; ++i) x = (lane >> 1) == i ? v[i] : x;
+    const unsigned half = (lane & 1) ? (unsigned)__double2hiint(x) : (unsigned)__double2loint(x);
+    if (lane < 2 * NV)
+      __hip_atomic_store((unsigned long long*)slots[rank].w[lane], ((unsigned long long)tag << 32) | half,
+                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-  if (!ok && threadIdx.x == 0) atomicOr(S.err_flag, (int)kTimeout);
-  return ok != 0;
+  // gather: with ACQ by one wave, which then fences for the workgroup, each
+  // lane taking up to four slots at a time; else by as many waves as there are
+  // 64 slots (fewer registers: the resident kernel has none to spare)
+  constexpr int GT = ACQ ? 64 : BLOCK;      // threads that gather
+  constexpr int GS = ACQ ? 4 : 1;           // slots in flight per thread
+  const bool gathers = wave * 64 < (ACQ ? 64 : S.team);
+  double s[NV];
+#pragma unroll
+  for (int i = 0; i < NV; ++i) s[i] = 0.0;
+  const int nb = Nbr::kAny && lane < 6 ? nbr.rank(lane) : -1;
+  if (gathers || Nbr::kAny) {
+    int b0 = gathers ? (int)threadIdx.x : S.team;
+    do {
+      double t[GS][NV];
+      long long t0 = 0;
+      while (true) {
+        asm volatile("" ::: "memory");      // every pass loads anew
+        bool all = true;
+        if (gathers) {
+#pragma unroll
+          for (int j = 0; j < GS; ++j) {
+            const int b = b0 + GT * j;      // (a slot past the bank reads 0)
+            const bool got = slot_ld<NV>(bank, b, tag, t[j]);
+            all &= got || b >= S.team;
+          }
+        }
+        if (nb >= 0) {
+          double u[NV];
+          all &= slot_ld<NV>(bank, nb, tag, u);
+        }
+        if (all) break;
+        const long long now = wall_clock64();
+        if (t0 == 0) t0 = now;
+        if (now - t0 > S.timeout_ticks) { ok = false; break; }
+      }
+#pragma unroll
+      for (int j = 0; j < GS; ++j) {
+        const int b = b0 + GT * j;
+#pragma unroll
+        for (int i = 0; i < NV; ++i) s[i] += b < S.team ? t[j][i] : 0.0;
+      }
+      b0 += GT * GS;
+    } while (b0 < S.team);
+  }
+  if constexpr (Nbr::kAny) nbr.ready();
+  if (gathers) {
+#pragma unroll
+    for (int i = 0; i < NV; ++i) s[i] = wave_sum(s[i]);
+    if (ACQ) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+  }
+  if (lane == 0 && (!ACQ || wave == 0)) {
+#pragma unroll
+    for (int i = 0; i < NV; ++i) rb.bc[wave][i] = s[i];
+  }
+  if (!ok) rb.bad[e & 1] = 1;
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < NV; ++i) v[i] = ACQ ? rb.bc[0][i] : row_sum<WAVES>(rb.bc[threadIdx.x & (WAVES - 1)][i]);
+  // (bad[e & 1] is cleared again two reductions later, after every thread read it here)
+  const bool fine = rb.bad[e & 1] == 0;
+  if (!fine && threadIdx.x == 0) atomicOr(S.err_flag, (int)kTimeout);
+  return fine;
 }
 
 // ---------------------------------------------------------------------------
@@ -1074,6 +1166,7 @@ __device__ __forceinline__ StepResult step_epilogue(const StepArgs<R>& S, const 
 
 template <typename R>
 __device__ __forceinline__ StepResult run_step(const StepArgs<R>& S, const StepVar<R>& V, int rank, Smem<R>& sh) {
+  constexpr int kB = Cfg<R>::kBlock;
   const Geom& g = S.g;
   const Coef<R> cf = coef_of(S);
   unsigned long long red = V.epoch_base;
@@ -1108,7 +1201,7 @@ __device__ __forceinline__ StepResult run_step(const StepArgs<R>& S, const StepV
       sweep<R>(g, rank, S.team, S.xcd_order, J, sh);
       stamp();
       double v2[2] = {J.acc[0], J.acc[1]};
-      ok &= team_sum<R, 2>(S, rank, red, v2, sh);
+      ok &= team_sum<R, 2, kB, true>(S, rank, red, v2, sh.rb);
       stamp();
       bb = v2[0];
       rr = v2[1];
@@ -1134,7 +1227,7 @@ __device__ __forceinline__ StepResult run_step(const StepArgs<R>& S, const StepV
     sweep<R>(g, rank, S.team, S.xcd_order, init, sh);
     stamp();
     double v3[3] = {init.acc[0], init.acc[1], init.acc[2]};
-    ok &= team_sum<R, 3>(S, rank, red, v3, sh);
+    ok &= team_sum<R, 3, kB, true>(S, rank, red, v3, sh.rb);
     stamp();
     bb = v3[0];
     double rz = v3[1];
@@ -1142,9 +1235,9 @@ __device__ __forceinline__ StepResult run_step(const StepArgs<R>& S, const StepV
 
     if (ok && bb == 0.0) {
       // b = 0: the solution is x = 0
-      own_cells(g, rank, S.team, S.xcd_order, [&](long long i, long long, int) { V.x[i] = R(0); });
+      own_cells(g, rank, S.team, S.xcd_order, [&](long long i, long long, int) { st_out(V.x + i, R(0)); });
       double v0[1] = {0.0};
-      ok &= team_sum<R, 1>(S, rank, red, v0, sh);
+      ok &= team_sum<R, 1, kB, true>(S, rank, red, v0, sh.rb);
       rr = 0.0;
     } else if (S.variant == 0) {
       R* pc = S.p0;
@@ -1174,7 +1267,7 @@ __device__ __forceinline__ StepResult run_step(const StepArgs<R>& S, const StepV
           sweep<R>(g, rank, S.team, S.xcd_order, C, sh);
           stamp();
           double vc[1] = {C.acc[0]};
-          ok &= team_sum<R, 1>(S, rank, red, vc, sh);
+          ok &= team_sum<R, 1, kB, true>(S, rank, red, vc, sh.rb);
           stamp();
           if (C.last) rz = vc[0];
         }
@@ -1191,7 +1284,7 @@ __device__ __forceinline__ StepResult run_step(const StepArgs<R>& S, const StepV
         sweep<R>(g, rank, S.team, S.xcd_order, A, sh);
         stamp();
         double v1[1] = {A.acc[0]};
-        ok &= team_sum<R, 1>(S, rank, red, v1, sh);
+        ok &= team_sum<R, 1, kB, true>(S, rank, red, v1, sh.rb);
         stamp();
         if (!ok) break;
         const double alpha_cg = rz / v1[0];
@@ -1204,7 +1297,7 @@ __device__ __forceinline__ StepResult run_step(const StepArgs<R>& S, const StepV
         sweep<R>(g, rank, S.team, S.xcd_order, B, sh);
         stamp();
         double v2[2] = {B.acc[0], B.acc[1]};
-        ok &= team_sum<R, 2>(S, rank, red, v2, sh);
+        ok &= team_sum<R, 2, kB, true>(S, rank, red, v2, sh.rb);
         stamp();
         rz_old = rz;
         rz = v2[0];
@@ -1222,7 +1315,7 @@ __device__ __forceinline__ StepResult run_step(const StepArgs<R>& S, const StepV
       sweep<R>(g, rank, S.team, S.xcd_order, W, sh);
       stamp();
       double vd[1] = {W.acc[0]};
-      ok &= team_sum<R, 1>(S, rank, red, vd, sh);
+      ok &= team_sum<R, 1, kB, true>(S, rank, red, vd, sh.rb);
       stamp();
       double gam = rz;
       double a_cg = gam / vd[0], b_cg = 0.0;
@@ -1250,7 +1343,7 @@ __device__ __forceinline__ StepResult run_step(const StepArgs<R>& S, const StepV
         a_pend = F.a;
         stamp();
         double v3n[3] = {F.acc[0], F.acc[1], F.acc[2]};
-        ok &= team_sum<R, 3>(S, rank, red, v3n, sh);
+        ok &= team_sum<R, 3, kB, true>(S, rank, red, v3n, sh.rb);
         stamp();
         ++it;
         cur ^= 1;
@@ -1271,7 +1364,7 @@ __device__ __forceinline__ StepResult run_step(const StepArgs<R>& S, const StepV
           st_out(xx + i, fma_r(ap, gld(pp, i), gld((const R*)xx, i)));
         });
         double vz[1] = {0.0};
-        ok &= team_sum<R, 1>(S, rank, red, vz, sh);
+        ok &= team_sum<R, 1, kB, true>(S, rank, red, vz, sh.rb);
       }
     }
   }

@@ -36,7 +36,6 @@ __device__ __forceinline__ void st_dev(float* p, float v) {
 __device__ __forceinline__ float ld_dev(const float* p) {
   return __hip_atomic_load(const_cast<float*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-constexpr int kCpolSc1 = 16;                // cache policy of a device-coherent load (sc1), as ld_dev
 
 // Buffer access to one FP32 vector of n elements: a lane's element offset
 // (bytes, per lane) plus a plane offset (bytes, uniform) -- no per-lane 64-bit
@@ -55,132 +54,13 @@ __device__ __forceinline__ void buf_st(__amdgpu_buffer_rsrc_t r, unsigned voff, 
   __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), r, voff, soff, CPOL);
 }
 
-struct ResRed {
-  double red[2][kMaxWaves][kNumRed];        // two buffers of per-wave partials (block_sum)
-  double bc[kNumRed];
-  int flag;
-};
-
 // LDS layout of the resident kernel (bytes).
 constexpr size_t kResAlphaFloats = (size_t)(kResTZ + 2) * kResPlane;   // alpha tile + halos
 constexpr int kResPZ = 3;                   // planes per barrier in one-vector sweeps
 constexpr size_t kResPlaneFloats = 2 * (size_t)kResPZ * kResPlane;     // [2 sets][kResPZ] or [2 vectors][2]
 constexpr size_t kResRingFloats = 3 * (size_t)kResTZ * kRing;          // [3 vectors][TZ][ring]
 constexpr size_t kResLdsBytes =
-    (kResAlphaFloats + kResPlaneFloats + kResRingFloats) * sizeof(float) + sizeof(ResRed) + 64;
-
-// Team reduction of the resident and blocked kernels. Every workgroup stores
-// its sum in its own slot, then EVERY workgroup gathers all slots and sums them
-// in the same fixed order, so all obtain bit-identical results after one
-// exchange (no master round trip). Each FP64 value travels as two 64-bit words
-// (tag << 32 | one half of its bits), the tag being the low 32 bits of the
-// reduction's epoch: a reader takes a slot's values and their validity in one
-// load round trip, and the writer issues its words without waiting between
-// them. Tags are unique between clears of the slots: an epoch is
-// (launch << 24) + k with k < 2^24 reductions per launch, and the host zeroes
-// the slots every 256 launches (tag 0 is never used) and whenever the slots
-// held the untagged layout of team_sum. Slots alternate between two banks by
-// epoch parity: a workgroup can be at most one reduction ahead of the slowest
-// reader (the next reduction needs every workgroup's slot), so a bank is
-// never rewritten while still read. Every value another workgroup reads was
-// written with device-scope stores, and every wave waits for its own stores
-// before the workgroup's block sum, so the tags are issued after the
-// workgroup's earlier stores have completed: the reduction doubles as the
-// team's barrier with no cache maintenance. Slots: 2 * team.
-struct alignas(64) TSlot {
-  unsigned long long w[2 * kNumRed];
-};
-static_assert(sizeof(TSlot) == sizeof(Slot), "the slot buffers are sized for either layout");
-
-__device__ __forceinline__ void st_tag(unsigned long long* p, unsigned long long v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// No work to start once the neighbours have published (see team_sum_dev).
-struct NoNeighbours {
-  __device__ int rank(int) const { return -1; }
-  __device__ void ready() const {}
-};
-
-// nbr.rank(k), k < 6, gives the ranks of the workgroups whose tiles share a
-// face with this one (-1: none); once every one of them has published its slot
-// for this reduction -- so their earlier stores are visible -- every wave calls
-// nbr.ready(), which may start loads of what the neighbours published, before
-// it gathers slots. (Keeping those loads to the waves that gather no slots
-// measured slower.)
-template <int NV, int BLOCK = kResBlock, class Nbr = NoNeighbours>
-__device__ __forceinline__ bool team_sum_dev(const StepArgs<float>& S, int rank, unsigned long long& epoch,
-                                             double (&v)[NV], ResRed* rs, const Nbr& nbr = Nbr()) {
-  static_assert(NV <= kNumRed, "slot too small");
-  __builtin_amdgcn_s_waitcnt(0);
-  block_sum<NV, BLOCK / 64>(v, rs->red[0]);
-  if (S.team == 1) {
-    __syncthreads();                        // red[0] is free again
-    return true;
-  }
-  const unsigned long long e = ++epoch;
-  const unsigned tag = (unsigned)e;
-  const unsigned long long th = (unsigned long long)tag << 32;
-  TSlot* slots = (TSlot*)S.slots + (size_t)(e & 1) * S.team;
-  if (threadIdx.x == 0) {
-#pragma unroll
-    for (int i = 0; i < NV; ++i) {
-      const unsigned long long bits = (unsigned long long)__double_as_longlong(v[i]);
-      st_tag(&slots[rank].w[2 * i], th | (bits & 0xffffffffull));
-      st_tag(&slots[rank].w[2 * i + 1], th | (bits >> 32));
-    }
-  }
-  int ok = 1;
-  {
-    // every wave waits (lanes 0-5) for the neighbours' slots, then starts its loads
-    const int k = threadIdx.x & 63;
-    const int b = k < 6 ? nbr.rank(k) : -1;
-    if (b >= 0 && b != rank) {
-      const long long t0 = wall_clock64();
-      while (true) {
-        bool all = true;
-#pragma unroll
-        for (int j = 0; j < 2 * NV; ++j) all &= (unsigned)(ld_epoch(&slots[b].w[j]) >> 32) == tag;
-        if (all) break;
-        __builtin_amdgcn_s_sleep(1);
-        if (wall_clock64() - t0 > S.timeout_ticks) { ok = 0; break; }
-      }
-    }
-    nbr.ready();
-  }
-  double s[NV];
-#pragma unroll
-  for (int i = 0; i < NV; ++i) s[i] = 0.0;
-  for (int b = threadIdx.x; b < S.team; b += BLOCK) {
-    if (b == rank) {
-#pragma unroll
-      for (int i = 0; i < NV; ++i) s[i] += v[i];
-      continue;
-    }
-    unsigned long long w[2 * NV];
-    const long long t0 = wall_clock64();
-    while (true) {
-      bool all = true;
-#pragma unroll
-      for (int k = 0; k < 2 * NV; ++k) {
-        w[k] = ld_epoch(&slots[b].w[k]);
-        all &= (unsigned)(w[k] >> 32) == tag;
-      }
-      if (all) break;
-      __builtin_amdgcn_s_sleep(1);
-      if (wall_clock64() - t0 > S.timeout_ticks) { ok = 0; break; }
-    }
-#pragma unroll
-    for (int i = 0; i < NV; ++i)
-      s[i] += __longlong_as_double((long long)((w[2 * i + 1] << 32) | (w[2 * i] & 0xffffffffull)));
-  }
-  ok = __syncthreads_and(ok);
-  block_sum<NV, BLOCK / 64>(s, rs->red[1]);
-#pragma unroll
-  for (int i = 0; i < NV; ++i) v[i] = s[i];
-  if (!ok && threadIdx.x == 0) atomicOr(S.err_flag, (int)kTimeout);
-  return ok != 0;
-}
+    (kResAlphaFloats + kResPlaneFloats + kResRingFloats) * sizeof(float) + sizeof(RedBuf) + 64;
 
 // Compile-time tile geometry: TX columns in x (a power of two), 512 / TX in y.
 template <int TX_>
@@ -405,6 +285,7 @@ __device__ __forceinline__ int neighbour_rank(const Geom& g, int tile, int team,
 // all published.
 template <typename F>
 struct ResNeighbours {
+  static constexpr bool kAny = true;
   const Geom& g;
   int tile, team, xcd;
   F ready_f;
@@ -489,7 +370,7 @@ __device__ __forceinline__ StepResult resident_step(const StepArgs<float>& S, co
   float* la = (float*)dsm;
   float* lp = la + kResAlphaFloats;
   float* lring = lp + kResPlaneFloats;
-  ResRed* rs = (ResRed*)(lring + kResRingFloats);
+  RedBuf& rb = *(RedBuf*)(lring + kResRingFloats);
 
   const Geom& g = S.g;
   // a caller that loops over steps must not keep the tile geometry of one
@@ -641,7 +522,7 @@ __device__ __forceinline__ StepResult resident_step(const StepArgs<float>& S, co
   }
   // the neighbours' u0 faces start loading into the u ring as soon as their
   // slots show that they are published (the set-up's x0 values there are used)
-  ok &= team_sum_dev<3>(S, rank, red, acc3, rs, res_neighbours(g, tile, S.team, S.xcd_order, [&]() {
+  ok &= team_sum<float, 3, kResBlock, false>(S, rank, red, acc3, rb, res_neighbours(g, tile, S.team, S.xcd_order, [&]() {
                           int tid_l = threadIdx.x, nxy_l = nxy;
                           asm volatile("" : "+v"(tid_l));
                           asm volatile("" : "+s"(nxy_l));
@@ -694,7 +575,7 @@ __device__ __forceinline__ StepResult resident_step(const StepArgs<float>& S, co
     float* ring_u = lring;
     float* ring_w = lring + kResTZ * kRing;
     float* ring_s = lring + 2 * kResTZ * kRing;
-    ok &= team_sum_dev<1>(S, rank, red, acc1, rs, res_neighbours(g, tile, S.team, S.xcd_order, [&]() {
+    ok &= team_sum<float, 1, kResBlock, false>(S, rank, red, acc1, rb, res_neighbours(g, tile, S.team, S.xcd_order, [&]() {
                             int tid_l = threadIdx.x, nxy_l = nxy;
                             asm volatile("" : "+v"(tid_l));
                             asm volatile("" : "+s"(nxy_l));
@@ -828,7 +709,7 @@ __device__ __forceinline__ StepResult resident_step(const StepArgs<float>& S, co
       if (S.trace_detail) stamp();
       // the next iteration's halo rings start loading as soon as the
       // neighbours have published this sweep's faces
-      ok &= team_sum_dev<3>(S, rank, red, acc, rs, res_neighbours(g, tile, S.team, S.xcd_order, [&]() {
+      ok &= team_sum<float, 3, kResBlock, false>(S, rank, red, acc, rb, res_neighbours(g, tile, S.team, S.xcd_order, [&]() {
                               int tid_r = threadIdx.x, nxy_r = nxy;
                               asm volatile("" : "+v"(tid_r));
                               asm volatile("" : "+s"(nxy_r));
@@ -884,7 +765,7 @@ __device__ __forceinline__ StepResult resident_step(const StepArgs<float>& S, co
       if (in && (q.edge || z == 0 || z + 1 == q.tzn)) st_dev(V.x + i, mcol[z]);
     }
     double dummy[1] = {0.0};
-    ok &= team_sum_dev<1>(S, rank, red, dummy, rs);
+    ok &= team_sum<float, 1, kResBlock, false>(S, rank, red, dummy, rb);
     float* ring_mu = lring;
     float* ring_T = lring + (size_t)kResTZ * kRing;
     fill_ring<G>(g, q, ring_mu, [&](int i) { return ld_dev(V.x + i); });
@@ -936,7 +817,7 @@ __device__ __forceinline__ StepResult resident_step(const StepArgs<float>& S, co
     // alternate between the two slot banks.
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
     double none[1] = {0.0};
-    if (!team_sum_dev<1>(S, rank, red, none, rs)) status |= kTimeout;
+    if (!team_sum<float, 1, kResBlock, false>(S, rank, red, none, rb)) status |= kTimeout;
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
   }
   const double relres = bb > 0.0 ? sqrt(rr / bb) : 0.0;

@@ -270,7 +270,7 @@ constexpr long long kResCells = 16384;        // cells of a full resident tile
 constexpr long long kResFixedCost = 24576;    // per resident iteration: reduction and face exchange
 constexpr int kBlock = nh::Cfg<float>::kBlock;
 static_assert(nhp::kBlock == kBlock && nhp::kResBlock == nh::kResBlock && nhp::kResTZ == nh::kResTZ &&
-                  nhp::kSlotBytes == sizeof(nh::Slot) && sizeof(nh::TSlot) == sizeof(nh::Slot),
+                  nhp::kSlotBytes == sizeof(nh::Slot),
               "the host-side policy must size jobs as the kernels tile them");
 
 double now_s() {
@@ -706,12 +706,12 @@ nh_status nh_server_tick(nh_server* s, int* n_active, int* n_queued, long long* 
     nh_status ts = ensure_tables(s, na);
     if (ts != NH_OK) return ts;
     const unsigned long long base = (++s->launch_ctr) << 24;
-    if (s->resident && (s->launch_ctr & 0xFF) == 0) {
+    if ((s->launch_ctr & 0xFF) == 0) {
       // the tagged reduction words repeat their tags every 256 launches:
       // zero every admitted job's slots before a new round starts
       for (size_t k = 0; k < na; ++k) {
         const SJob* j = s->active[k];
-        SV_HIP(s, hipMemsetAsync(j->slots, 0, sizeof(nh::TSlot) * (2 * (size_t)j->team + 2), s->stream));
+        SV_HIP(s, hipMemsetAsync(j->slots, 0, sizeof(nh::Slot) * (2 * (size_t)j->team + 2), s->stream));
       }
     }
     int nb = 0;
