@@ -12,6 +12,7 @@
 #include "nh_kernels.hpp"
 #include "nh_resident.hpp"
 #include "nh_jacobi.hpp"
+#include "nh_brick.hpp"
 #include "nh_tv.hpp"
 #include "nh_proj.hpp"
 
@@ -109,6 +110,15 @@ struct Buf {
   size_t bytes = 0;
 };
 
+// Consecutive steps waiting to be launched together by nh::brick_steps_kernel.
+template <typename R>
+struct BrickQueue {
+  nh::BrickSteps<R> tab{};
+  StepArgs<R> base{};
+  const int* iters[nh::kBrickSteps] = {};    // where each step writes its iteration count
+  int ev = -1;                               // event slot of the first queued step (-1: none)
+};
+
 }  // namespace
 
 struct nh_ctx {
@@ -148,6 +158,7 @@ struct nh_ctx {
   Buf xface;                                 // resident kernel: compact x-edge columns of u, w/D, s/D
   Buf srcq, srcqt;                           // source gradients: dL/dq^n series, q_t on the device
   double* scratch = nullptr;                 // this device's scratch array (nh_tv_noalloc)
+  Buf halo;                                  // brick kernel: tagged halo words
   Buf jt[2];                                 // tagged iterates of the blocked fixed-K kernel
   unsigned jt_tag = 1;                       // tag of the next launch's first phase (0: cleared)
   // steps of the blocked fixed-K kernel waiting to be launched together
@@ -155,6 +166,8 @@ struct nh_ctx {
   nh::StepArgs<float> jq_base{};
   int jq_ev = -1;                            // event slot of the first queued step (-1: none)
   unsigned long long jq_epoch = 0;
+  BrickQueue<float> bq32;
+  BrickQueue<double> bq64;
   Buf mu[nh::kProjRing];                     // adjoint states, mu^n in mu[n % ring] (ring 4, or 8 with
                                              //   the projected guess)
   Buf pguess, ppart, pstate;                 // projected guess: A v, then x0; dot partials; ProjState
@@ -168,6 +181,8 @@ struct nh_ctx {
   bool resident = false;                     // the current plan uses nh::resident_step_kernel
   bool jac_tb = false;                       // the current plan uses nh::jacobi_step_kernel
   int jtx = 0, jty = 0;                      //   with this many interior tiles per axis
+  int brick_nt = 0, brick_zc = 0;            // the current plan uses nh::brick_steps_kernel (0: not) with
+                                             //   this many threads and cells per thread
   unsigned long long launch_ctr = 0;         // makes every launch's reduction epochs unique
   size_t ws_bytes = 0, ws_peak = 0;
 
@@ -250,12 +265,100 @@ nh_status fill(nh_ctx* c, T* p, long long n, T v) {
   return NH_OK;
 }
 
+// A brick kernel: threads, cells per thread, and the time of an iteration (us)
+// that a small team of such workgroups takes for FP32 and FP64 (0: not built),
+// measured on 32x32x16 (16x16x8 for the single workgroup).
+struct BrickOpt {
+  int nt, zc;
+  double us32, us64;
+};
+constexpr BrickOpt kBrickOpts[] = {
+    {512, 1, 3.65, 3.5}, {512, 2, 3.8, 3.7}, {512, 4, 4.2, 4.2}, {512, 8, 5.4, 0.0}, {256, 8, 4.75, 4.95}};
+
+template <typename R>
+const void* brick_kernel(int nt, int zc) {
+  if (nt == 512 && zc == 1) return (const void*)nh::brick_steps_kernel<R, 1, 512>;
+  if (nt == 512 && zc == 2) return (const void*)nh::brick_steps_kernel<R, 2, 512>;
+  if (nt == 512 && zc == 4) return (const void*)nh::brick_steps_kernel<R, 4, 512>;
+  if (nt == 256 && zc == 8) return (const void*)nh::brick_steps_kernel<R, 8, 256>;
+  if constexpr (sizeof(R) == 4) {
+    if (nt == 512 && zc == 8) return (const void*)nh::brick_steps_kernel<float, 8, 512>;
+  }
+  return nullptr;
+}
+
+BrickQueue<float>& brick_queue(nh_ctx* c, float) { return c->bq32; }
+BrickQueue<double>& brick_queue(nh_ctx* c, double) { return c->bq64; }
+
+// Bricks for the current grid and vectors of `size` bytes per element
+// (nh_brick.hpp), for the single-reduction CG with automatic tiling; false if
+// they need more workgroups than there are CUs. Of all brick shapes the one with
+// the smallest modelled iteration is taken: the kernel's time, plus what the
+// reduction's gather costs per workgroup (64x64x32 FP32: 128 bricks of two
+// planes 4.0 us, 256 of one plane 5.1, 64 of four planes 4.4; 96x96x32: 144
+// bricks of 32 x 16 columns 4.9, 192 of 64 x 8 5.2), less the exchange where
+// one brick holds the grid (16x16x8: one workgroup 2.5 us, two 3.6); among
+// equals the widest (coalesced edges: 100x75x30 4.9 us with 64 columns, 5.1
+// with 32).
+bool plan_brick(nh_ctx* c, int size) {
+  if (c->variant != 2 || c->jacobi_k > 0 || c->tile_z > 0 || c->team_max > 0 || c->trace_step > 0) return false;
+  double best = 1e30;
+  Geom bg{};
+  for (const BrickOpt& o : kBrickOpts) {
+    const double us = size == 4 ? o.us32 : o.us64;
+    if (us == 0.0) continue;
+    for (int txs = 4; txs <= 6; ++txs) {
+      Geom g{};
+      g.nx = c->nx;
+      g.ny = c->ny;
+      g.nz = c->nz;
+      g.nxy = (long long)c->nx * c->ny;
+      g.ng = g.nxy * c->nz;
+      g.periodic = c->periodic;
+      g.txs = txs;
+      g.TX = 1 << txs;
+      g.TY = o.nt >> txs;
+      g.ntx = (g.nx + g.TX - 1) / g.TX;
+      g.nty = (g.ny + g.TY - 1) / g.TY;
+      const int nz_t = (g.nz + o.zc - 1) / o.zc;
+      g.TZ = (g.nz + nz_t - 1) / nz_t;
+      g.ntz = (g.nz + g.TZ - 1) / g.TZ;
+      const long long nt = (long long)g.ntx * g.nty * g.ntz;
+      if (nt > c->num_cu) continue;
+      g.ntiles = (int)nt;
+      const double cost =
+          us + 0.002 * (double)nt + 0.006 * (double)std::max(0LL, nt - 128) - (nt == 1 ? 2.2 : 0.0) + 0.03 * (6 - txs);
+      if (cost < best) {
+        best = cost;
+        bg = g;
+        c->brick_nt = o.nt;
+        c->brick_zc = o.zc;
+      }
+    }
+  }
+  if (best >= 1e30) return false;
+  c->geom = bg;
+  c->team = bg.ntiles;
+  c->resident = c->jac_tb = false;
+  c->st.team_blocks = c->team;
+  c->st.block_threads = c->brick_nt;
+  c->st.tile_x = bg.TX;
+  c->st.tile_y = bg.TY;
+  c->st.tile_z = bg.TZ;
+  c->st.resident = size == 4 && !c->periodic && c->robin == 0 ? 1 : 0;
+  c->st.resident_occupancy = c->res_occ;
+  c->st.jacobi_blocked = 0;
+  return true;
+}
+
 // Tile shape and team size for the current grid, for workgroups of `block`
 // threads; resident_ok allows the register-resident kernel (FP32, variant 2,
 // zero-flux walls and the CG inner solver), tb_ok the temporally blocked
 // fixed-K kernel (FP32, fixed-K sweeps, nz <= 16, automatic tiling, one
 // interior tile per workgroup within what fits on the chip).
-void plan(nh_ctx* c, int occ, int block, bool resident_ok = false, bool tb_ok = false) {
+void plan(nh_ctx* c, int occ, int block, bool resident_ok = false, bool tb_ok = false, int brick_size = 0) {
+  c->brick_nt = c->brick_zc = 0;
+  if (brick_size > 0 && plan_brick(c, brick_size)) return;
   resident_ok = resident_ok && !c->periodic && c->robin == 0 && c->jacobi_k == 0;
   c->jac_tb = false;
   if (tb_ok && c->jacobi_k > 0 && c->nz <= nh::kJacNZ && c->tile_z == 0 && c->jac_occ > 0) {
@@ -387,14 +490,65 @@ int occupancy(nh_ctx* c) {
 // slots are zeroed when a launch starts a new round of 256, so no stale word
 // can carry the tag a reader waits for.
 nh_status prepare_slots(nh_ctx* c, unsigned long long epoch_base) {
-  if (((epoch_base >> 24) & 0xFF) == 0)
-    NH_TRY(fill<unsigned long long>(c, (unsigned long long*)c->slots.p, (long long)(c->slots.bytes / 8), 0ull));
+  if (((epoch_base >> 24) & 0xFF) != 0) return NH_OK;
+  if (c->halo.p)                             // the brick kernel's halo words carry the same tags
+    NH_TRY(fill<unsigned long long>(c, (unsigned long long*)c->halo.p, (long long)(c->halo.bytes / 8), 0ull));
+  NH_TRY(fill<unsigned long long>(c, (unsigned long long*)c->slots.p, (long long)(c->slots.bytes / 8), 0ull));
+  return NH_OK;
+}
+
+// Launch the queued brick steps as one launch, timed with the event pair of
+// the first of them.
+template <typename R>
+nh_status flush_brick(nh_ctx* c, BrickQueue<R>& q) {
+  if (q.tab.count == 0) return NH_OK;
+  NH_TRY(prepare_slots(c, q.tab.v[0].epoch_base));
+  const bool timed = c->profile && q.ev >= 0;
+  if (timed) NH_HIP(c, hipEventRecord(c->ev[2 * q.ev], c->stream));
+  void* args[] = {(void*)&q.base, (void*)&q.tab};
+  NH_HIP(c, hipLaunchCooperativeKernel(brick_kernel<R>(c->brick_nt, c->brick_zc), dim3(q.base.team),
+                                       dim3(c->brick_nt), args, 0, c->stream));
+  if (timed) {
+    NH_HIP(c, hipEventRecord(c->ev[2 * q.ev + 1], c->stream));
+    c->ev_rec[q.ev] = 1;
+  }
+  ++c->kernel_launches;
+  q.tab.count = 0;
+  q.ev = -1;
+  return NH_OK;
+}
+
+// Queue one brick step; steps of one sweep share everything but their StepVar fields.
+template <typename R>
+nh_status queue_brick(nh_ctx* c, const StepArgs<R>& S, int slot_ev) {
+  BrickQueue<R>& q = brick_queue(c, R(0));
+  // (a launch carries the state from step to step)
+  if (q.tab.count > 0 && (S.mode != q.base.mode || S.G != q.base.G || S.xprev != q.tab.v[q.tab.count - 1].x))
+    NH_TRY(flush_brick(c, q));
+  const int n = q.tab.count;
+  if (n == 0) {
+    q.base = S;
+    q.ev = slot_ev;
+  }
+  q.tab.v[n] = nh::step_var(S);
+  q.iters[n] = S.out_iters;
+  for (int d = 0; d < 3; ++d) {
+    q.tab.lg[n][d] = -1;
+    for (int j = 0; j < n && S.gmode < 0; ++j)
+      if (q.iters[j] == S.gi + S.gp[d]) q.tab.lg[n][d] = (signed char)j;
+  }
+  ++q.tab.count;
+  // (a launch's reductions stay below 2^24 epochs)
+  if (q.tab.count == nh::kBrickSteps || (long long)(q.tab.count + 1) * ((long long)S.max_iter + 8) >= (1 << 24))
+    NH_TRY(flush_brick(c, q));
   return NH_OK;
 }
 
 // Launch the queued steps of the blocked fixed-K kernel as one launch, timed
 // with the event pair of the first of them.
 nh_status flush_steps(nh_ctx* c) {
+  NH_TRY(flush_brick(c, c->bq32));
+  NH_TRY(flush_brick(c, c->bq64));
   if (c->jq.count == 0) return NH_OK;
   NH_TRY(prepare_slots(c, c->jq_epoch));
   hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -448,6 +602,7 @@ nh_status queue_step(nh_ctx* c, StepArgs<float>& S, int slot_ev, bool* launched)
 
 template <typename R>
 nh_status launch_step(nh_ctx* c, StepArgs<R>& S, int slot_ev, double* t_kernel) {
+  if (c->brick_nt > 0) return queue_brick<R>(c, S, slot_ev);
   if constexpr (sizeof(R) == 4) {
     if (c->jac_tb && !S.trace) {
       bool launched = false;
@@ -539,6 +694,7 @@ void base_args(nh_ctx* c, StepArgs<R>& S, double dt) {
   S.s0 = (R*)c->vs0.p;
   S.s1 = (R*)c->vs1.p;
   S.xface = (R*)c->xface.p;
+  S.halo = c->halo.p;
   S.variant = c->variant == 0 ? 0 : 1;
   S.jacobi_k = c->jacobi_k;
   S.jtx = c->jac_tb ? c->jtx : 0;
@@ -722,6 +878,13 @@ nh_status ensure_common(nh_ctx* c, int nsteps) {
     NH_HIP(c, hipMemsetAsync(c->flag.p, 0, 64, c->stream));
   }
   NH_TRY(ensure(c, c->steps, step_out_bytes(nsteps)));
+  if (c->brick_nt > 0) {                     // two banks of w/D, one of u0
+    const size_t hb = 3 * 2 * sizeof(R) * (size_t)c->geom.ng;
+    if (c->halo.bytes < hb) {
+      NH_TRY(ensure(c, c->halo, hb));
+      NH_TRY(fill<unsigned long long>(c, (unsigned long long*)c->halo.p, (long long)(c->halo.bytes / 8), 0ull));
+    }
+  }
   if (c->jac_tb) {
     const size_t tb = sizeof(unsigned long long) * (size_t)c->geom.ng;
     if (c->jt[0].bytes < tb || c->jt[1].bytes < tb) {
@@ -858,7 +1021,7 @@ nh_status do_forward(nh_ctx* c, const R* alpha, const R* q_xy, const double* q_t
 
   drop_forward(c);
   plan(c, occupancy<R>(c), nh::Cfg<R>::kBlock, sizeof(R) == 4 && c->variant == 2 && c->res_occ > 0,
-       sizeof(R) == 4);
+       sizeof(R) == 4, sizeof(R));
   NH_TRY(ensure_common<R>(c, nsteps));
   NH_TRY(ensure_events(c));
   const Geom& g = c->geom;
@@ -1068,6 +1231,7 @@ nh_status do_adjoint(nh_ctx* c, const R* gsurf, double* G, R* dq, R* dT0) {
       NH_TRY(collect_events(c, used, &tk));
       used = 0;
     }
+    if (proj) NH_TRY(flush_steps(c));       // the projection reads mu^n
     if (proj && n > 1) NH_TRY(proj_prepare<R>(c, n, N, M, gsurf + (size_t)(n - 2) * g.nxy, dt));
     return NH_OK;
   };
@@ -1404,6 +1568,26 @@ nh_status nh_apply_A(nh_ctx* c, const float* alpha, const float* x, float* y, do
   if (!alpha || !x || !y) return fail(c, NH_EINVAL, "null pointer argument");
   if (x == y) return fail(c, NH_EINVAL, "y must not alias x");
   if (!(dt >= 0) || !std::isfinite(dt)) return fail(c, NH_EINVAL, "dt must be finite and >= 0");
+  // a saved forward keeps its own plan for its adjoint
+  struct Plan {
+    nh_ctx* c;
+    Geom geom;
+    nh_stats st;
+    int team, brick_nt, brick_zc;
+    bool resident, jac_tb;
+    explicit Plan(nh_ctx* k)
+        : c(k), geom(k->geom), st(k->st), team(k->team), brick_nt(k->brick_nt), brick_zc(k->brick_zc),
+          resident(k->resident), jac_tb(k->jac_tb) {}
+    ~Plan() {
+      c->geom = geom;
+      c->st = st;
+      c->team = team;
+      c->brick_nt = brick_nt;
+      c->brick_zc = brick_zc;
+      c->resident = resident;
+      c->jac_tb = jac_tb;
+    }
+  } const saved(c);
   plan(c, c->occ_f32, nh::Cfg<float>::kBlock);
   const Geom& g = c->geom;
   const int blocks = std::min(g.ntiles, std::max(1, c->occ_f32 * c->num_cu));
@@ -1515,7 +1699,7 @@ void nh_destroy(nh_ctx* c) {
   (void)hipStreamSynchronize(c->stream);
   Buf* bufs[] = {&c->trace, &c->alpha, &c->qxy, &c->z, &c->p0, &c->p1, &c->u1, &c->vw0, &c->vw1,
                  &c->vs0, &c->vs1, &c->traj, &c->seg, &c->slots, &c->steps, &c->flag, &c->tvpart, &c->srcq, &c->srcqt,
-                 &c->jt[0], &c->jt[1], &c->pguess, &c->ppart, &c->pstate, &c->dmaxb, &c->xface};
+                 &c->jt[0], &c->jt[1], &c->pguess, &c->ppart, &c->pstate, &c->dmaxb, &c->xface, &c->halo};
   for (Buf* b : bufs) release(c, *b);
   for (Buf& b : c->mu) release(c, b);
   for (Buf& b : c->w) release(c, b);

@@ -6,11 +6,10 @@
 // step's epilogue (surface frame and checkpoint in the forward sweep, the
 // gradient accumulation in the adjoint sweep). The workgroups of a launch form
 // a "team" that synchronises only through FP64 reductions: every workgroup
-// publishes its partial sums in a slot of its own, one master workgroup waits
-// for all slots, sums them in a fixed order and publishes the result. No
-// read-modify-write atomics are involved (no contention on one address, which
-// grows linearly with the team), every workgroup receives the same bits, and a
-// rerun is bit-identical.
+// publishes its partial sums in a slot of its own and gathers all slots in the
+// same fixed order (team_sum). No read-modify-write atomics are involved (no
+// contention on one address, which grows linearly with the team), every
+// workgroup receives the same bits, and a rerun is bit-identical.
 //
 // CG in the form used here (M = diag(A), the Jacobi preconditioner of
 // App. D.2, as a preconditioner instead of as the solver):
@@ -91,6 +90,7 @@ struct StepArgs {
   R* s0;
   R* s1;
   R* xface;                                 // resident kernel: compact x-edge columns (nh_resident.hpp)
+  void* halo;                               // brick kernel: tagged halo words, three banks (nh_brick.hpp)
   int variant;                              // 0: two reductions per iteration, 1: one
   int jacobi_k;                             // > 0: K Jacobi sweeps from h1 instead of CG
   int jtx, jty;                             // temporally blocked fixed-K kernel: interior tiles per axis,
@@ -208,41 +208,35 @@ __device__ __forceinline__ R diag_of(R c0, R c1, R c2, R c3, R c4, R c5, R sk) {
   return R(1) + ((((c0 + c1) + (c2 + c3)) + (c4 + c5)) + sk);
 }
 
-// Sum over the 64 lanes, the result in every lane: a butterfly (partners 32,
-// 16, 8, 4, 2, 1 lanes apart) in registers. The halves and the 16-lane rows are
-// exchanged by the lane-swap instructions; within a row the values repeat
-// after each stage, so a rotation by the stage's distance reaches the partner's
-// value. The LDS-permute form of the same butterfly pays an LDS round trip per
-// stage; in the team reduction, which runs four stages of it one after the
-// other, it took 2.4 of 4.4 us (two workgroups).
-template <int CTRL>
-__device__ __forceinline__ double row_ror(double v) {
-  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, false);
-  return __hiloint2double(hi, lo);
-}
-// Sum over groups of N = 2, 4, 8 or 16 lanes of a row whose values repeat
-// with period N (N = 16: any values), the result in every lane.
-template <int N>
-__device__ __forceinline__ double row_sum(double v) {
-  if (N >= 16) v += row_ror<0x128>(v);
-  if (N >= 8) v += row_ror<0x124>(v);
-  if (N >= 4) v += row_ror<0x122>(v);
-  if (N >= 2) v += row_ror<0x121>(v);
+__device__ __forceinline__ double wave_sum(double v) {
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
   return v;
 }
-__device__ __forceinline__ double wave_sum(double v) {
-  {
-    const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(v), __double2loint(v), false, false);
-    const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(v), __double2hiint(v), false, false);
-    v = __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
-  }
-  {
-    const auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(v), __double2loint(v), false, false);
-    const auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(v), __double2hiint(v), false, false);
-    v = __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
-  }
-  return row_sum<16>(v);
+
+// Sums over the 64 lanes of up to four values at once, the results in every
+// lane, by the FP64 matrix instruction D = A B + C (16 x 4 times 4 x 16; lane l
+// holds A[l % 16][l / 16], B[l / 16][l % 16] and D[4 r + l / 16][l % 16], r < 4).
+// One product per value with B = 1 in the value's four columns adds the four
+// lanes of each row; three additions add the four rows a lane holds; and a last
+// product with B = 1 adds the four lanes left per value and hands all results
+// to all lanes. The chain is a few matrix instructions long, where a
+// butterfly is six exchanges and additions per value (three values, eight waves:
+// 1720 cycles as a butterfly in registers, and more through LDS permutes).
+// All lanes of the wave must call it.
+typedef double double4v __attribute__((ext_vector_type(4)));
+template <int NV>
+__device__ __forceinline__ void wave_sums(double (&v)[NV]) {
+  static_assert(NV <= 4, "four columns per value");
+  const int col = (threadIdx.x & 15) >> 2;
+  double4v d = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int i = 0; i < NV; ++i) d = __builtin_amdgcn_mfma_f64_16x16x4f64(v[i], col == i ? 1.0 : 0.0, d, 0, 0, 0);
+  const double t = (d[0] + d[1]) + (d[2] + d[3]);
+  const double4v z = {0.0, 0.0, 0.0, 0.0};
+  d = __builtin_amdgcn_mfma_f64_16x16x4f64(t, 1.0, z, 0, 0, 0);
+#pragma unroll
+  for (int i = 0; i < NV; ++i) v[i] = d[i];
 }
 
 // ---------------------------------------------------------------------------
@@ -267,11 +261,10 @@ __device__ __forceinline__ double wave_sum(double v) {
 // read what others stored with ordinary (cached) loads.
 //
 // What bounds it is latency: the stores' completion, one store and one load to
-// the device's coherence point, two workgroup barriers. One wave polls, with
-// three 16-byte loads per slot instead of six 8-byte ones from eight waves: on
-// 3 values, 512 threads, 256 workgroups 2.7 us instead of 9.6 (64: 2.2 / 5.1,
-// 2: 1.9 / 4.4; of the difference the wave sums' registers butterfly makes
-// 2.4-4.6 us, the wide loads the rest).
+// the device's coherence point, two workgroup barriers and what is added in
+// between. With three values and 512 threads, alone: 2.7 us on 256 workgroups,
+// 1.9 us on two, where LDS-permute butterflies and 8-byte slot loads took 9.6
+// and 4.4 us.
 
 struct alignas(64) Slot {
   unsigned w[2 * kNumRed][2];               // (half of the value's bits, tag)
@@ -294,13 +287,18 @@ struct Smem {
   RedBuf rb;
 };
 
-// The sum over a workgroup's waves of the partials in rb.red, in every lane.
+// The sums over a workgroup's waves of the partials p[wave][value], in every
+// lane (rows 4 i .. 4 i + 3 of A hold value i, four waves per product).
 template <int NV, int WAVES>
-__device__ __forceinline__ void cross_wave_sum(const RedBuf& rb, double (&v)[NV]) {
-  static_assert(WAVES == 4 || WAVES == 8 || WAVES == 16, "one row of lanes holds the waves' sums");
-  const int w = threadIdx.x & (WAVES - 1);
+__device__ __forceinline__ void cross_wave_sums(const double (*p)[kNumRed], double (&v)[NV]) {
+  static_assert(WAVES % 4 == 0 && kNumRed == 4, "four waves per product, four values per wave");
+  const int lane = threadIdx.x & 63;
+  double4v d = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-  for (int i = 0; i < NV; ++i) v[i] = row_sum<WAVES>(rb.red[w][i]);
+  for (int w = 0; w < WAVES; w += 4)
+    d = __builtin_amdgcn_mfma_f64_16x16x4f64(p[w + (lane >> 4)][(lane & 15) >> 2], 1.0, d, 0, 0, 0);
+#pragma unroll
+  for (int i = 0; i < NV; ++i) v[i] = d[i];
 }
 
 constexpr int kCpolSc1 = 16;                // cache policy of a device-coherent access (sc1)
@@ -312,29 +310,32 @@ __device__ __forceinline__ bool slot_ld(__amdgpu_buffer_rsrc_t bank, int b, unsi
 #pragma unroll
   for (int i = 0; i < NV; ++i) {
     const auto x = __builtin_amdgcn_raw_buffer_load_b128(bank, b * (int)sizeof(Slot) + 16 * i, 0, kCpolSc1);
-    all &= x[1] == tag && x[3] == tag;
+    all &= (x[1] == tag) & (x[3] == tag);
     v[i] = __hiloint2double((int)x[2], (int)x[0]);
   }
   return all;
 }
 
-// No work to start once the neighbours have published (see team_sum).
+// What a reduction waits for beside the slots, and starts then (see team_sum):
+// nothing, here.
 struct NoNeighbours {
   static constexpr bool kAny = false;
-  __device__ int rank(int) const { return -1; }
+  template <int NV> __device__ bool poll(__amdgpu_buffer_rsrc_t, unsigned) const { return true; }
   __device__ void ready() const {}
 };
 
-// Team all-reduce of NV doubles; also the team's barrier. nbr.rank(k), k < 6,
-// gives the ranks of the workgroups whose tiles share a face with this one (-1:
-// none); once every one of them has published its slot for this reduction -- so
-// their earlier stores are visible -- every wave calls nbr.ready(), which may
-// start loads of what the neighbours published (a wave that gathers slots polls
-// both together). Waits are bounded by timeout_ticks; a timeout returns false in every thread of the
-// workgroup and is recorded in err_flag.
-template <typename R, int NV, int BLOCK, bool ACQ, class Nbr = NoNeighbours>
+// Team all-reduce of NV doubles; also the team's barrier for everything that
+// was stored before it (without WAIT only for stores that carry tags of their
+// own). Every wave polls nbr.poll(bank, tag) together with the slots it gathers
+// until it returns true in all lanes, then calls nbr.ready(): the resident kernel
+// waits there for its face neighbours' slots and starts loads of what they
+// published, the brick kernel loads the tagged halo values themselves. Waits
+// are bounded by timeout_ticks; a timeout returns false in every thread of the
+// workgroup and is recorded in err_flag; so does ok = false in any thread (an
+// earlier wait that timed out).
+template <typename R, int NV, int BLOCK, bool ACQ, class Nbr = NoNeighbours, bool WAIT = true>
 __device__ __forceinline__ bool team_sum(const StepArgs<R>& S, int rank, unsigned long long& epoch,
-                                         double (&v)[NV], RedBuf& rb, const Nbr& nbr = Nbr()) {
+                                         double (&v)[NV], RedBuf& rb, const Nbr& nbr = Nbr(), bool ok = true) {
   static_assert(NV <= kNumRed, "slot too small");
   constexpr int WAVES = BLOCK / 64;
   const int lane = threadIdx.x & 63;
@@ -342,26 +343,26 @@ __device__ __forceinline__ bool team_sum(const StepArgs<R>& S, int rank, unsigne
   const unsigned long long e = ++epoch;
   if (threadIdx.x == 0) rb.bad[e & 1] = 0;
   // every wave's stores (device-coherent) complete before the slot is published
-  __builtin_amdgcn_s_waitcnt(0);
-#pragma unroll
-  for (int i = 0; i < NV; ++i) v[i] = wave_sum(v[i]);
+  if (WAIT) __builtin_amdgcn_s_waitcnt(0);
+  wave_sums<NV>(v);
   if (lane == 0) {
 #pragma unroll
     for (int i = 0; i < NV; ++i) rb.red[wave][i] = v[i];
   }
   __syncthreads();
   if (S.team == 1) {
-    cross_wave_sum<NV, WAVES>(rb, v);
+    cross_wave_sums<NV, WAVES>(rb.red, v);
     __syncthreads();                        // rb.red is free again
-    return true;
+    return ok;
   }
-  const unsigned tag = (unsigned)e;
-  Slot* slots = (Slot*)S.slots + (size_t)(e & 1) * S.team;
+  // (uniform, and marked so: a buffer resource in vector registers would turn
+  // every load into a loop of its own, one round trip after the other)
+  const unsigned tag = __builtin_amdgcn_readfirstlane((unsigned)e);
+  Slot* slots = (Slot*)S.slots + (size_t)(tag & 1) * S.team;
   const __amdgpu_buffer_rsrc_t bank =
       __builtin_amdgcn_make_buffer_rsrc(slots, 0, S.team * (int)sizeof(Slot), 0x00020000);
-  bool ok = true;
   if (wave == 0) {
-    cross_wave_sum<NV, WAVES>(rb, v);
+    cross_wave_sums<NV, WAVES>(rb.red, v);
     // lane j stores word j of the slot: value j / 2, its low or high half
     double x = v[0];
 #pragma unroll
@@ -380,27 +381,23 @@ __device__ __forceinline__ bool team_sum(const StepArgs<R>& S, int rank, unsigne
   double s[NV];
 #pragma unroll
   for (int i = 0; i < NV; ++i) s[i] = 0.0;
-  const int nb = Nbr::kAny && lane < 6 ? nbr.rank(lane) : -1;
   if (gathers || Nbr::kAny) {
-    int b0 = gathers ? (int)threadIdx.x : S.team;
+    int b0 = threadIdx.x;
     do {
       double t[GS][NV];
       long long t0 = 0;
       while (true) {
         asm volatile("" ::: "memory");      // every pass loads anew
+        // no branches among the loads and tests of a pass: it is one round
+        // trip, where a branch between two loads makes it two
         bool all = true;
-        if (gathers) {
 #pragma unroll
-          for (int j = 0; j < GS; ++j) {
-            const int b = b0 + GT * j;      // (a slot past the bank reads 0)
-            const bool got = slot_ld<NV>(bank, b, tag, t[j]);
-            all &= got || b >= S.team;
-          }
+        for (int j = 0; j < GS; ++j) {
+          const int b = b0 + GT * j;        // (a slot past the bank reads 0)
+          const bool got = slot_ld<NV>(bank, b, tag, t[j]);
+          all &= got | (b >= S.team);
         }
-        if (nb >= 0) {
-          double u[NV];
-          all &= slot_ld<NV>(bank, nb, tag, u);
-        }
+        all &= nbr.template poll<NV>(bank, tag);
         if (all) break;
         const long long now = wall_clock64();
         if (t0 == 0) t0 = now;
@@ -417,8 +414,7 @@ __device__ __forceinline__ bool team_sum(const StepArgs<R>& S, int rank, unsigne
   }
   if constexpr (Nbr::kAny) nbr.ready();
   if (gathers) {
-#pragma unroll
-    for (int i = 0; i < NV; ++i) s[i] = wave_sum(s[i]);
+    wave_sums<NV>(s);
     if (ACQ) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
   }
   if (lane == 0 && (!ACQ || wave == 0)) {
@@ -427,8 +423,12 @@ __device__ __forceinline__ bool team_sum(const StepArgs<R>& S, int rank, unsigne
   }
   if (!ok) rb.bad[e & 1] = 1;
   __syncthreads();
+  if constexpr (ACQ) {
 #pragma unroll
-  for (int i = 0; i < NV; ++i) v[i] = ACQ ? rb.bc[0][i] : row_sum<WAVES>(rb.bc[threadIdx.x & (WAVES - 1)][i]);
+    for (int i = 0; i < NV; ++i) v[i] = rb.bc[0][i];
+  } else {
+    cross_wave_sums<NV, WAVES>(rb.bc, v);
+  }
   // (bad[e & 1] is cleared again two reductions later, after every thread read it here)
   const bool fine = rb.bad[e & 1] == 0;
   if (!fine && threadIdx.x == 0) atomicOr(S.err_flag, (int)kTimeout);
@@ -1087,7 +1087,7 @@ __device__ __forceinline__ int guess_order(const StepVar<R>& V) {
   }
   if (!V.xprev || !V.xprev2) return 0;
   if (o == 2 && !V.xprev3) o = 1;
-  return o;
+  return __builtin_amdgcn_readfirstlane(o);   // uniform: it selects the vectors to load
 }
 
 // (e1, e2) of x0 = e1 h1 + e2 h2 (+ h3) for guess orders 1..3 (order 3: 0 h1 + h2
@@ -1162,6 +1162,17 @@ __device__ __forceinline__ StepResult step_epilogue(const StepArgs<R>& S, const 
     V.out_status[0] = status;
   }
   return StepResult{it, status, relres, 0ull};
+}
+
+// The scalars of the single-reduction iteration from its new sums gn = u.r and
+// dn = u.w: b = gn / gam, a = gn / (dn - b gn / a), gam = gn. The first two
+// divisions are written to be independent, since the chain from the sums to a
+// is exposed in every iteration.
+__device__ __forceinline__ void cg_scalars(double gn, double dn, double& gam, double& a, double& b) {
+  const double q = gn / a;
+  b = gn / gam;
+  a = gn / (dn - b * q);
+  gam = gn;
 }
 
 template <typename R>
@@ -1350,9 +1361,7 @@ __device__ __forceinline__ StepResult run_step(const StepArgs<R>& S, const StepV
         rr = v3n[2];
         if (!(rr > S.rtol2 * bb)) break;
         const double gn = v3n[0], dn = v3n[1];
-        b_cg = gn / gam;
-        a_cg = gn / (dn - b_cg * gn / a_cg);
-        gam = gn;
+        cg_scalars(gn, dn, gam, a_cg, b_cg);
       }
       if (xpend && ok) {
         // the last iteration's x += a p (p holds its p), then a team barrier:

@@ -280,21 +280,25 @@ __device__ __forceinline__ int neighbour_rank(const Geom& g, int tile, int team,
   return t;
 }
 
-// The tagged reduction's early hook of the resident step: the neighbours'
-// ranks and `ready`, which the reduction calls in every wave once they have
-// all published.
+// The reduction's early hook of the resident step: once the face neighbours'
+// slots are there -- so their earlier stores are visible -- every wave calls
+// ready_f.
 template <typename F>
 struct ResNeighbours {
   static constexpr bool kAny = true;
-  const Geom& g;
-  int tile, team, xcd;
+  int nb;                                   // lanes 0-5: a neighbour's rank (-1 none)
   F ready_f;
-  __device__ int rank(int k) const { return neighbour_rank(g, tile, team, xcd, k); }
+  template <int NV> __device__ bool poll(__amdgpu_buffer_rsrc_t bank, unsigned tag) const {
+    double t[NV];
+    const bool got = slot_ld<NV>(bank, nb < 0 ? 0x100000 : nb, tag, t);   // (past the bank: reads 0)
+    return got | (nb < 0);
+  }
   __device__ void ready() const { ready_f(); }
 };
 template <typename F>
 __device__ __forceinline__ ResNeighbours<F> res_neighbours(const Geom& g, int tile, int team, int xcd, F f) {
-  return ResNeighbours<F>{g, tile, team, xcd, f};
+  const int lane = threadIdx.x & 63;
+  return ResNeighbours<F>{lane < 6 ? neighbour_rank(g, tile, team, xcd, lane) : -1, f};
 }
 
 // Compact copies of the tiles' x-edge columns, which the x neighbours load
@@ -729,9 +733,7 @@ __device__ __forceinline__ StepResult resident_step(const StepArgs<float>& S, co
       rr = acc[2];
       if (!(rr > S.rtol2 * bb)) break;
       const double gn = acc[0], dn = acc[1];
-      b_cg = gn / gam;
-      a_cg = gn / (dn - b_cg * gn / a_cg);
-      gam = gn;
+      cg_scalars(gn, dn, gam, a_cg, b_cg);
     }
     // the halo loads started in the last reduction land before LDS is reused
     __builtin_amdgcn_s_waitcnt(0);

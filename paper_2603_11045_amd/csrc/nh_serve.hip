@@ -205,7 +205,8 @@ __global__ void __launch_bounds__(Cfg<float>::kBlock, 1) batch_run_kernel(const 
                                                                           JobProg* prog) {
   __shared__ Smem<float> sh;
   __shared__ SliceState ss;
-  const int2 m = map[blockIdx.x];
+  const int2 mv = map[blockIdx.x];
+  const int2 m = make_int2(__builtin_amdgcn_readfirstlane(mv.x), __builtin_amdgcn_readfirstlane(mv.y));
   if (m.x < 0) return;
   // The job table is not written during the launch: reading it through the
   // constant address space makes its loads scalar and invariant.
@@ -221,7 +222,8 @@ __global__ void __launch_bounds__(kResBlock, 1) batch_resident_kernel(const JobR
                                                                        JobProg* prog) {
   extern __shared__ __align__(16) unsigned char dsm[];
   __shared__ SliceState ss;
-  const int2 m = map[blockIdx.x];
+  const int2 mv = map[blockIdx.x];
+  const int2 m = make_int2(__builtin_amdgcn_readfirstlane(mv.x), __builtin_amdgcn_readfirstlane(mv.y));
   if (m.x < 0) return;
   const CJobRun& J = *(const CJobRun*)(jobs + m.x);
   run_slice(J, m, prog, &ss, [&](const StepArgs<float>& S, const StepVar<float>& V) {
