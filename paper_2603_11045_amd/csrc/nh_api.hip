@@ -128,7 +128,6 @@ struct nh_ctx {
   long long wallclock_khz = 100000;
   int occ_f32 = 0, occ_f64 = 0;              // co-resident step kernels per CU
   int res_occ = 0;                           // co-resident resident kernels per CU (0: unusable)
-  int jac_occ = 0;                           // co-resident temporally blocked fixed-K kernels per CU
 
   bool grid_set = false;
   int nx = 0, ny = 0, nz = 0;
@@ -159,6 +158,7 @@ struct nh_ctx {
   Buf srcq, srcqt;                           // source gradients: dL/dq^n series, q_t on the device
   double* scratch = nullptr;                 // this device's scratch array (nh_tv_noalloc)
   Buf halo;                                  // brick kernel: tagged halo words
+  Buf jpart;                                 // blocked fixed-K kernel: residual sums by step and workgroup
   Buf jt[2];                                 // tagged iterates of the blocked fixed-K kernel
   unsigned jt_tag = 1;                       // tag of the next launch's first phase (0: cleared)
   // steps of the blocked fixed-K kernel waiting to be launched together
@@ -179,7 +179,8 @@ struct nh_ctx {
   double cheb_dmax = 1.0;                    // max D of the saved forward's operator (Chebyshev interval)
   Buf dmaxb;                                 // device result of nh::dmax_kernel
   bool resident = false;                     // the current plan uses nh::resident_step_kernel
-  bool jac_tb = false;                       // the current plan uses nh::jacobi_step_kernel
+  bool jac_tb = false;                       // the current plan uses the blocked fixed-K kernels
+  int jac_iy = 0;                            //   on interior tiles of this many rows
   int jtx = 0, jty = 0;                      //   with this many interior tiles per axis
   int brick_nt = 0, brick_zc = 0;            // the current plan uses nh::brick_steps_kernel (0: not) with
                                              //   this many threads and cells per thread
@@ -263,6 +264,24 @@ nh_status fill(nh_ctx* c, T* p, long long n, T v) {
   hipLaunchKernelGGL(nh::fill_kernel<T>, dim3(blocks), dim3(256), 0, c->stream, p, n, v);
   NH_HIP(c, hipGetLastError());
   return NH_OK;
+}
+
+// The blocked fixed-K kernel for interior tiles of iy rows and nz planes, and its threads.
+struct JacKernel {
+  const void* fn;
+  int threads;
+};
+JacKernel jacobi_kernel(int iy, int nz) {
+  if (nz <= nh::kJacNZ)
+    return {iy == 2   ? (const void*)nh::jacobi_steps_kernel<2>
+            : iy == 4 ? (const void*)nh::jacobi_steps_kernel<4>
+                      : (const void*)nh::jacobi_steps_kernel<8>,
+            nh::jac_threads(2, iy)};
+  if (nz <= 24)
+    return {iy == 2 ? (const void*)nh::jacobi_deep_kernel<12, 2, 2> : (const void*)nh::jacobi_deep_kernel<8, 3, 4>,
+            nh::jac_threads(iy == 2 ? 2 : 3, iy)};
+  if (iy == 2) return {(const void*)nh::jacobi_deep_kernel<16, 2, 2>, nh::jac_threads(2, 2)};
+  return {(const void*)nh::jacobi_deep_kernel<16, 2, 4>, nh::jac_threads(2, 4)};
 }
 
 // A brick kernel: threads, cells per thread, and the time of an iteration (us)
@@ -354,20 +373,26 @@ bool plan_brick(nh_ctx* c, int size) {
 // Tile shape and team size for the current grid, for workgroups of `block`
 // threads; resident_ok allows the register-resident kernel (FP32, variant 2,
 // zero-flux walls and the CG inner solver), tb_ok the temporally blocked
-// fixed-K kernel (FP32, fixed-K sweeps, nz <= 16, automatic tiling, one
-// interior tile per workgroup within what fits on the chip).
+// fixed-K kernels (FP32, fixed-K sweeps, nz <= 32, automatic tiling, one
+// interior tile per workgroup and CU), brick_size the brick kernel.
 void plan(nh_ctx* c, int occ, int block, bool resident_ok = false, bool tb_ok = false, int brick_size = 0) {
   c->brick_nt = c->brick_zc = 0;
   if (brick_size > 0 && plan_brick(c, brick_size)) return;
   resident_ok = resident_ok && !c->periodic && c->robin == 0 && c->jacobi_k == 0;
   c->jac_tb = false;
-  if (tb_ok && c->jacobi_k > 0 && c->nz <= nh::kJacNZ && c->tile_z == 0 && c->jac_occ > 0) {
-    const int jtx = (c->nx + nh::kJacIX - 1) / nh::kJacIX, jty = (c->ny + nh::kJacIY - 1) / nh::kJacIY;
-    const long long nt = (long long)jtx * jty;
-    long long cap = (long long)c->num_cu * c->jac_occ;
+  if (tb_ok && c->jacobi_k > 0 && c->nz <= nh::kJacNZDeep && c->tile_z == 0) {
+    // the lowest interior tiles that leave every workgroup a CU: their sweeps
+    // are the shortest (64x64x16, K = 50: 1.46 us per sweep with tiles of 2
+    // rows, 1.70 with 4, 2.45 with 8; 75x50x24: 2.10 with 2, 2.71 with 4, 9.6 in
+    // the streaming kernel)
+    long long cap = c->num_cu;
     if (c->team_max > 0) cap = std::min<long long>(cap, c->team_max);
-    if (nt <= cap) {
-      // the epilogue (surface frame, checkpoint, gradient pass) marches 64 x 8 x nz tiles
+    const int jtx = (c->nx + nh::kJacIX - 1) / nh::kJacIX;
+    int iy = 2;
+    while (iy <= 8 && (long long)jtx * ((c->ny + iy - 1) / iy) > cap) iy *= 2;
+    const int jty = (c->ny + iy - 1) / iy;
+    const long long nt = (long long)jtx * jty;
+    if (iy <= (c->nz > nh::kJacNZ ? 4 : 8) && 8 * (long long)c->nx * c->ny * c->nz < (1LL << 31)) {
       Geom g{};
       g.nx = c->nx;
       g.ny = c->ny;
@@ -375,29 +400,17 @@ void plan(nh_ctx* c, int occ, int block, bool resident_ok = false, bool tb_ok = 
       g.nxy = (long long)c->nx * c->ny;
       g.ng = g.nxy * c->nz;
       g.periodic = c->periodic;
-      g.TX = 64;
-      g.TY = nh::kJacBlock / 64;
-      g.txs = 6;
-      g.ntx = (g.nx + g.TX - 1) / g.TX;
-      g.nty = (g.ny + g.TY - 1) / g.TY;
-      {
-        // split in z so that the team shares the gradient pass
-        const long long xy = (long long)g.ntx * g.nty;
-        const long long want_ntz = std::max<long long>(1, (nt + xy - 1) / xy);
-        g.TZ = (int)std::max<long long>(1, (g.nz + want_ntz - 1) / want_ntz);
-      }
-      g.ntz = (g.nz + g.TZ - 1) / g.TZ;
-      g.ntiles = g.ntx * g.nty * g.ntz;
       c->geom = g;
       c->team = (int)nt;
       c->jac_tb = true;
+      c->jac_iy = iy;
       c->jtx = jtx;
       c->jty = jty;
       c->resident = false;
       c->st.team_blocks = c->team;
-      c->st.block_threads = nh::kJacBlock;
+      c->st.block_threads = jacobi_kernel(iy, c->nz).threads;
       c->st.tile_x = nh::kJacIX;
-      c->st.tile_y = nh::kJacIY;
+      c->st.tile_y = iy;
       c->st.tile_z = c->nz;
       c->st.resident = 0;
       c->st.resident_occupancy = c->res_occ;
@@ -558,8 +571,8 @@ nh_status flush_steps(nh_ctx* c) {
     NH_HIP(c, hipEventRecord(e0, c->stream));
   }
   void* args[] = {(void*)&c->jq_base, (void*)&c->jq};
-  NH_HIP(c, hipLaunchCooperativeKernel((const void*)nh::jacobi_steps_kernel<nh::kJacH>, dim3(c->jq_base.team),
-                                       dim3(nh::kJacBlock), args, 0, c->stream));
+  const JacKernel k = jacobi_kernel(c->jac_iy, c->nz);
+  NH_HIP(c, hipLaunchCooperativeKernel(k.fn, dim3(c->jq_base.team), dim3(k.threads), args, 0, c->stream));
   if (e1) {
     NH_HIP(c, hipEventRecord(e1, c->stream));
     c->ev_rec[c->jq_ev] = 1;
@@ -570,18 +583,17 @@ nh_status flush_steps(nh_ctx* c) {
   return NH_OK;
 }
 
-// Queue one step of the blocked fixed-K kernel. Steps of one sweep share
-// everything but their StepVar fields; step i of a launch gets the epoch
-// base B + i (B even), so consecutive steps' final reductions use
-// alternating slot banks. Returns in *launched whether the step was
-// launched now (the caller's event slot is then used).
+// Queue one step of the blocked fixed-K kernel; steps of one sweep share
+// everything but their StepVar fields. Returns in *launched whether the step
+// was launched now (the caller's event slot is then used).
 nh_status queue_step(nh_ctx* c, StepArgs<float>& S, int slot_ev, bool* launched) {
   const unsigned phases = (unsigned)((S.jacobi_k + nh::kJacS - 1) / nh::kJacS);
-  if (c->jq.count > 0 && (S.mode != c->jq_base.mode || S.G != c->jq_base.G || S.alpha != c->jq_base.alpha))
+  // (a launch carries the state from step to step)
+  if (c->jq.count > 0 && (S.mode != c->jq_base.mode || S.G != c->jq_base.G || S.xprev != c->jq.v[c->jq.count - 1].x))
     NH_TRY(flush_steps(c));
   if (c->jt_tag > 0xFFFFFFF0u - phases) {
     NH_TRY(flush_steps(c));
-    for (Buf& b : c->jt) NH_TRY(fill<unsigned long long>(c, (unsigned long long*)b.p, c->geom.ng, 0ull));
+    for (Buf& b : c->jt) NH_TRY(fill<unsigned long long>(c, (unsigned long long*)b.p, (long long)(b.bytes / 8), 0ull));
     c->jt_tag = 1;
   }
   S.jt[0] = (unsigned long long*)c->jt[0].p;
@@ -592,7 +604,7 @@ nh_status queue_step(nh_ctx* c, StepArgs<float>& S, int slot_ev, bool* launched)
     c->jq_epoch = (++c->launch_ctr) << 24;
     c->jq_ev = slot_ev;
   }
-  S.epoch_base = c->jq_epoch + (unsigned long long)c->jq.count;
+  S.epoch_base = c->jq_epoch;
   if (c->jq.count == 0) c->jq_base = S;
   c->jq.v[c->jq.count++] = nh::step_var(S);
   *launched = c->jq.count == nh::kJacBatch;
@@ -604,7 +616,7 @@ template <typename R>
 nh_status launch_step(nh_ctx* c, StepArgs<R>& S, int slot_ev, double* t_kernel) {
   if (c->brick_nt > 0) return queue_brick<R>(c, S, slot_ev);
   if constexpr (sizeof(R) == 4) {
-    if (c->jac_tb && !S.trace) {
+    if (c->jac_tb && (!S.trace || c->nz > nh::kJacNZ)) {
       bool launched = false;
       NH_TRY(queue_step(c, S, slot_ev, &launched));
       (void)t_kernel;
@@ -634,8 +646,10 @@ nh_status launch_step(nh_ctx* c, StepArgs<R>& S, int slot_ev, double* t_kernel) 
     S.jt[1] = (unsigned long long*)c->jt[1].p;
     S.jtag = c->jt_tag;
     c->jt_tag += phases;
-    NH_HIP(c, hipLaunchCooperativeKernel((const void*)nh::jacobi_step_kernel<nh::kJacH>, dim3(S.team),
-                                         dim3(nh::kJacBlock), args, 0, c->stream));
+    const void* f = c->jac_iy == 2   ? (const void*)nh::jacobi_step_kernel<2>
+                    : c->jac_iy == 4 ? (const void*)nh::jacobi_step_kernel<4>
+                                     : (const void*)nh::jacobi_step_kernel<8>;
+    NH_HIP(c, hipLaunchCooperativeKernel(f, dim3(S.team), dim3(jacobi_kernel(c->jac_iy, c->nz).threads), args, 0, c->stream));
   }
   else
     NH_HIP(c, hipLaunchCooperativeKernel((const void*)nh::step_kernel<R>, dim3(S.team), dim3(nh::Cfg<R>::kBlock),
@@ -695,6 +709,7 @@ void base_args(nh_ctx* c, StepArgs<R>& S, double dt) {
   S.s1 = (R*)c->vs1.p;
   S.xface = (R*)c->xface.p;
   S.halo = c->halo.p;
+  S.jpart = (double*)c->jpart.p;
   S.variant = c->variant == 0 ? 0 : 1;
   S.jacobi_k = c->jacobi_k;
   S.jtx = c->jac_tb ? c->jtx : 0;
@@ -886,6 +901,7 @@ nh_status ensure_common(nh_ctx* c, int nsteps) {
     }
   }
   if (c->jac_tb) {
+    NH_TRY(ensure(c, c->jpart, sizeof(double) * 2 * nh::kJacBatch * (size_t)c->team));
     const size_t tb = sizeof(unsigned long long) * (size_t)c->geom.ng;
     if (c->jt[0].bytes < tb || c->jt[1].bytes < tb) {
       for (Buf& b : c->jt) NH_TRY(ensure(c, b, tb));
@@ -967,20 +983,19 @@ nh_status forward_step(nh_ctx* c, int n, const R* const (&h)[3], R* x, const R* 
     // sweep(s) and reduction(s): two pairs (variant 0) or one pair (variant 1)
     const double us = 1e3 / (double)c->wallclock_khz;
     if (c->jac_tb) {
-      // stamps: start, set-up, then per phase: iterate loaded, sweeps done, barrier passed
+      // stamps: start, set-up, then per phase: sweeps done, interior stored and halo loaded
       const long long* t = tall.data();
       int m = 0;
       while (m < cap && t[m] != 0) ++m;
-      double ld = 0, sw = 0, br = 0;
-      const int np = m > 2 ? (m - 2) / 3 : 0;
+      double sw = 0, ex = 0;
+      const int np = m > 2 ? (m - 2) / 2 : 0;
       for (int k = 0; k < np; ++k) {
-        ld += (t[2 + 3 * k] - t[1 + 3 * k]) * us;
-        sw += (t[3 + 3 * k] - t[2 + 3 * k]) * us;
-        br += (t[4 + 3 * k] - t[3 + 3 * k]) * us;
+        sw += (t[2 + 2 * k] - t[1 + 2 * k]) * us;
+        ex += (t[3 + 2 * k] - t[2 + 2 * k]) * us;
       }
       std::fprintf(stderr, "[nh trace] step %d rank %d blocked fixed-K: set-up %.2f us, %d phases, mean us per phase: "
-                   "load %.2f, sweeps %.2f, store+barrier %.2f\n", n, S.trace_rank, m > 1 ? (t[1] - t[0]) * us : 0.0,
-                   np, np ? ld / np : 0.0, np ? sw / np : 0.0, np ? br / np : 0.0);
+                   "sweeps %.2f, store+load %.2f\n", n, S.trace_rank, m > 1 ? (t[1] - t[0]) * us : 0.0,
+                   np, np ? sw / np : 0.0, np ? ex / np : 0.0);
       return NH_OK;
     }
     const int head = c->variant == 0 ? 3 : 5, per = c->variant == 0 ? 4 : (S.trace_detail ? 5 : 2);
@@ -1455,11 +1470,6 @@ nh_status nh_create(nh_ctx** out, int hip_device, void* hip_stream) {
     (void)hipGetLastError();
     if (std::getenv("NH_TRACE_STEP"))
       std::fprintf(stderr, "[nh] resident kernel: %zu B LDS, %d workgroups per CU\n", nh::kResLdsBytes, c->res_occ);
-    int jo = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&jo, (const void*)nh::jacobi_step_kernel<nh::kJacH>,
-                                                     nh::kJacBlock, 0) == hipSuccess)
-      c->jac_occ = jo;
-    (void)hipGetLastError();
   }
   if (scratch_of(hip_device, &c->scratch) != hipSuccess) {
     delete c;
@@ -1699,7 +1709,7 @@ void nh_destroy(nh_ctx* c) {
   (void)hipStreamSynchronize(c->stream);
   Buf* bufs[] = {&c->trace, &c->alpha, &c->qxy, &c->z, &c->p0, &c->p1, &c->u1, &c->vw0, &c->vw1,
                  &c->vs0, &c->vs1, &c->traj, &c->seg, &c->slots, &c->steps, &c->flag, &c->tvpart, &c->srcq, &c->srcqt,
-                 &c->jt[0], &c->jt[1], &c->pguess, &c->ppart, &c->pstate, &c->dmaxb, &c->xface, &c->halo};
+                 &c->jt[0], &c->jt[1], &c->pguess, &c->ppart, &c->pstate, &c->dmaxb, &c->xface, &c->halo, &c->jpart};
   for (Buf* b : bufs) release(c, *b);
   for (Buf& b : c->mu) release(c, b);
   for (Buf& b : c->w) release(c, b);

@@ -96,6 +96,7 @@ struct StepArgs {
   int jtx, jty;                             // temporally blocked fixed-K kernel: interior tiles per axis,
   unsigned long long* jt[2];                //   its tagged iterate buffers (value | tag << 32) and the
   unsigned jtag;                            //   tag of this launch's first phase
+  double* jpart;                            //   [steps][team][2] residual sums by workgroup
   const R* top_src;                         // [ny][nx] added on k = 0 (forward q_xy, adjoint g^n)
   R top_scale;                              // forward dt*q_t[n-1], adjoint 1
   R* surf_out;                              // frame of the solution on k = 0 (or null), times
@@ -145,6 +146,13 @@ template <> __device__ __forceinline__ double rcp<double>(double v) { return 1.0
 template <typename T>
 __device__ __forceinline__ void st_out(T* p, T v) {
   __hip_atomic_store((__attribute__((address_space(1))) T*)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// A device-coherent load of what another workgroup stored so.
+template <typename T>
+__device__ __forceinline__ T ld_out(const T* p) {
+  return __hip_atomic_load((__attribute__((address_space(1))) T*)const_cast<T*>(p), __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // A product and a sum rounded on their own, never fused into a multiply-add
@@ -228,13 +236,17 @@ typedef double double4v __attribute__((ext_vector_type(4)));
 template <int NV>
 __device__ __forceinline__ void wave_sums(double (&v)[NV]) {
   static_assert(NV <= 4, "four columns per value");
-  const int col = (threadIdx.x & 15) >> 2;
+  // (laundered: the operand of ones and zeros is not held through the callers' loops)
+  int col = (threadIdx.x & 15) >> 2;
+  double one = 1.0;
+  asm volatile("" : "+v"(col));
+  asm volatile("" : "+v"(one));
   double4v d = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-  for (int i = 0; i < NV; ++i) d = __builtin_amdgcn_mfma_f64_16x16x4f64(v[i], col == i ? 1.0 : 0.0, d, 0, 0, 0);
+  for (int i = 0; i < NV; ++i) d = __builtin_amdgcn_mfma_f64_16x16x4f64(v[i], col == i ? one : 0.0, d, 0, 0, 0);
   const double t = (d[0] + d[1]) + (d[2] + d[3]);
   const double4v z = {0.0, 0.0, 0.0, 0.0};
-  d = __builtin_amdgcn_mfma_f64_16x16x4f64(t, 1.0, z, 0, 0, 0);
+  d = __builtin_amdgcn_mfma_f64_16x16x4f64(t, one, z, 0, 0, 0);
 #pragma unroll
   for (int i = 0; i < NV; ++i) v[i] = d[i];
 }
@@ -291,12 +303,18 @@ struct Smem {
 // lane (rows 4 i .. 4 i + 3 of A hold value i, four waves per product).
 template <int NV, int WAVES>
 __device__ __forceinline__ void cross_wave_sums(const double (*p)[kNumRed], double (&v)[NV]) {
-  static_assert(WAVES % 4 == 0 && kNumRed == 4, "four waves per product, four values per wave");
-  const int lane = threadIdx.x & 63;
+  static_assert(kNumRed == 4, "four waves per product, four values per wave");
+  int lane = threadIdx.x & 63;
+  double one = 1.0;
+  asm volatile("" : "+v"(lane));
+  asm volatile("" : "+v"(one));
   double4v d = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-  for (int w = 0; w < WAVES; w += 4)
-    d = __builtin_amdgcn_mfma_f64_16x16x4f64(p[w + (lane >> 4)][(lane & 15) >> 2], 1.0, d, 0, 0, 0);
+  for (int w = 0; w < WAVES; w += 4) {
+    const int i = w + (lane >> 4);
+    const double a = WAVES % 4 == 0 || i < WAVES ? p[i][(lane & 15) >> 2] : 0.0;
+    d = __builtin_amdgcn_mfma_f64_16x16x4f64(a, one, d, 0, 0, 0);
+  }
 #pragma unroll
   for (int i = 0; i < NV; ++i) v[i] = d[i];
 }
@@ -512,6 +530,11 @@ template <>
 __device__ __forceinline__ double plane_ld<double>(__amdgpu_buffer_rsrc_t r, unsigned off) {
   const auto v = __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0);
   return __hiloint2double((int)v[1], (int)v[0]);
+}
+
+// One FP32 value at a lane's byte offset (kOffLane: 0) plus a uniform one.
+__device__ __forceinline__ float plane_ld_at(__amdgpu_buffer_rsrc_t r, unsigned voff, int soff) {
+  return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, voff, soff, 0));
 }
 
 // March one tile along z. Op supplies: NL vectors loaded at the staged cells
