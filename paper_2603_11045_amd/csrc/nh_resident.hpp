@@ -303,12 +303,13 @@ __device__ __forceinline__ ResNeighbours<F> res_neighbours(const Geom& g, int ti
 
 // Compact copies of the tiles' x-edge columns, which the x neighbours load
 // into their halo rings: [bank][tile][side][vector][kResTZ][8] floats, side 0
-// the tile's first column in x, 1 its last, vectors u, w/D, s/D. Eight planes
+// the tile's first column in x, 1 its last, vectors u0 and w/D. Eight planes
 // of one column are 64 consecutive floats, one load of a wave (in the vectors
 // themselves consecutive values of a column lie nx floats apart, a cache line
 // each); the offsets of a tile's vectors and planes are constants.
 constexpr int kXfCol = kResTZ * 8;          // floats of one column
-constexpr int kXfTile = 2 * 3 * kXfCol;     // floats per tile and bank
+constexpr int kXfVec = 2;                   // vectors
+constexpr int kXfTile = 2 * kXfVec * kXfCol;   // floats per tile and bank
 // column (tile 0, side 0) of vector vec in bank `bank`
 __device__ __forceinline__ float* xface_of(float* xf, int team, int vec, int bank) {
   return xf + (size_t)bank * team * kXfTile + (size_t)vec * kXfCol;
@@ -353,7 +354,7 @@ __device__ __forceinline__ void ring_dma(const Geom& g, const ResPos& q, float* 
   if (cz < q.tzn && cx >= 0 && cx < g.nx && cy < g.ny) {
     // from the compact copy: the neighbour's facing column (its first for +x,
     // its last for -x), planes 8 b .. 8 b + 7, 64 consecutive floats
-    const float* s = xsrc ? xsrc + (size_t)(2 * (xp ? tile + g.ntz : tile - g.ntz) + (xp ? 0 : 1)) * (3 * kXfCol) +
+    const float* s = xsrc ? xsrc + (size_t)(2 * (xp ? tile + g.ntz : tile - g.ntz) + (xp ? 0 : 1)) * (kXfVec * kXfCol) +
                                 64 * b + lane
                           : bz + ((long long)cz * nxy + cx + (long long)g.nx * cy);
     __builtin_amdgcn_global_load_lds(s, ring + (xp ? kRingXp : kRingXm) + 64 * b, 4, 0, kCpolSc1);
@@ -515,7 +516,7 @@ __device__ __forceinline__ StepResult resident_step(const StepArgs<float>& S, co
   // publish u0 on the tile's faces (x-edge columns: the compact copy)
   float* const xf = XF ? S.xface : nullptr;
   const bool fedge = XF ? q.yedge : q.edge;   // face cells stored in the vectors
-  const int xfo = (2 * tile + q.xside) * (3 * kXfCol) + q.ty;   // the column's row, bank 0 vector 0
+  const int xfo = (2 * tile + q.xside) * (kXfVec * kXfCol) + q.ty;   // the column's row, bank 0 vector 0
   if (q.own) {
 #pragma unroll
     for (int z = 0; z < TZ; ++z)
@@ -539,9 +540,7 @@ __device__ __forceinline__ StepResult resident_step(const StepArgs<float>& S, co
   const double bb = acc3[0];
   double gam = acc3[1], rr = acc3[2];
 
-  float* ub[2] = {S.z, S.u1};
   float* wb[2] = {S.w0, S.w1};
-  float* sb[2] = {S.s0, S.s1};
   int it = 0, status = kOk;
   if (!(ok && bb != 0.0 && rr > S.rtol2 * bb)) {
     __builtin_amdgcn_s_waitcnt(0);          // no solve: the u ring's loads end before LDS is reused
@@ -557,8 +556,8 @@ __device__ __forceinline__ StepResult resident_step(const StepArgs<float>& S, co
     rr = 0.0;
   } else if (ok && rr > S.rtol2 * bb) {
     // ---------------- w0 = A u0
-    if (q.own && q.bot_z) zlo[0] = ld_dev(ub[0] + q.col + (T.z0 - 1) * nxy);
-    if (q.own && q.top_z) zhi[0] = ld_dev(ub[0] + q.col + T.z1 * nxy);
+    if (q.own && q.bot_z) zlo[0] = ld_dev(S.z + q.col + (T.z0 - 1) * nxy);
+    if (q.own && q.top_z) zhi[0] = ld_dev(S.z + q.col + T.z1 * nxy);
     __builtin_amdgcn_s_waitcnt(0);          // the u ring has landed
     __syncthreads();
     double acc1[1] = {0.0};
@@ -574,8 +573,8 @@ __device__ __forceinline__ StepResult resident_step(const StepArgs<float>& S, co
                      if (XF && q.xside >= 0) st_dev(xface_of(xf, S.team, 1, 0) + xfo + 8 * z, wr[z]);
                    });
     stamp();
-    // the first iteration's halo rings (u0, w0/D; no s yet) start loading as
-    // soon as the neighbours have published
+    // the first iteration's halo of w0/D starts loading as soon as the
+    // neighbours have published (u0 is there, s starts from zero)
     float* ring_u = lring;
     float* ring_w = lring + kResTZ * kRing;
     float* ring_s = lring + 2 * kResTZ * kRing;
@@ -583,7 +582,6 @@ __device__ __forceinline__ StepResult resident_step(const StepArgs<float>& S, co
                             int tid_l = threadIdx.x, nxy_l = nxy;
                             asm volatile("" : "+v"(tid_l));
                             asm volatile("" : "+s"(nxy_l));
-                            // (u0 is in ring_u already)
                             if constexpr (XF)
                               ring_dma<G>(g, q, ring_w, wb[0], tid_l, nxy_l, xface_of(xf, S.team, 1, 0), tile);
                             else
@@ -592,6 +590,7 @@ __device__ __forceinline__ StepResult resident_step(const StepArgs<float>& S, co
     stamp();
     double a_cg = gam / acc1[0], b_cg = 0.0;
     int cur = 0;
+    float zsl = 0.f, zsh = 0.f;             // s below and above the tile (u is in zlo[0], zhi[0])
     while (ok) {
       if (it >= S.max_iter) { status |= kNoConv; break; }
       // keep per-plane address arithmetic inside the loop (hoisting it for every
@@ -608,25 +607,15 @@ __device__ __forceinline__ StepResult resident_step(const StepArgs<float>& S, co
       asm volatile("" : "+s"(ql.tzn));
       asm volatile("" : "+s"(z0_l));
       const float a = (float)a_cg, b = (float)b_cg;
-      const bool first = it == 0;
-      // the neighbours' published u, w/D, s/D on the tile's ring are on their
-      // way to LDS already (started inside the last reduction); the values
-      // below and above the tile are loaded now and land while the registers
-      // are updated
-      const float* uo = ub[cur];
+      // the neighbours' published w/D on the tile's ring is on its way to LDS
+      // already (started inside the last reduction); the values below and above
+      // the tile are loaded now and land while the registers are updated
       const float* wo = wb[cur];
-      const float* so = sb[cur];
       int tid_l = threadIdx.x;
       asm volatile("" : "+v"(tid_l));
-      float zl[3] = {0.f, 0.f, 0.f}, zh[3] = {0.f, 0.f, 0.f};
-      if (q.own && q.bot_z) {
-        const int i = col_l + (T.z0 - 1) * nxy_l;
-        zl[0] = ld_dev(uo + i); zl[1] = ld_dev(wo + i); zl[2] = first ? 0.f : ld_dev(so + i);
-      }
-      if (q.own && q.top_z) {
-        const int i = col_l + T.z1 * nxy_l;
-        zh[0] = ld_dev(uo + i); zh[1] = ld_dev(wo + i); zh[2] = first ? 0.f : ld_dev(so + i);
-      }
+      float zwl = 0.f, zwh = 0.f;
+      if (q.own && q.bot_z) zwl = ld_dev(wo + col_l + (T.z0 - 1) * nxy_l);
+      if (q.own && q.top_z) zwh = ld_dev(wo + col_l + T.z1 * nxy_l);
       // elementwise updates: s = w + b s, p = u + b p, u -= a s in registers
       // (x += a p follows plane by plane in the sweep, where its memory
       // traffic hides behind the stencil's arithmetic). In the first
@@ -640,31 +629,32 @@ __device__ __forceinline__ StepResult resident_step(const StepArgs<float>& S, co
         sr[z] = s_;
         ur[z] = fmaf(-a, s_, ur[z]);
       }
-      // halo values of the new u from the neighbours' published u, w/D, s/D
-      // (first iteration: b = 0 and the s values are zeros)
-      auto unew = [&](float u_, float w_, float s_) { return fmaf(-a, fmaf(b, s_, w_), u_); };
-      zlo[0] = unew(zl[0], zl[1], zl[2]);
-      zhi[0] = unew(zh[0], zh[1], zh[2]);
+      // the halo's s and u advance by the same operations as their owner's, so
+      // w/D is all that is exchanged
+      zsl = fmaf(b, zsl, zwl);
+      zsh = fmaf(b, zsh, zwh);
+      zlo[0] = fmaf(-a, zsl, zlo[0]);
+      zhi[0] = fmaf(-a, zsh, zhi[0]);
       if (S.trace_detail) stamp();
       __builtin_amdgcn_s_waitcnt(0);        // the ring loads have reached LDS
       __syncthreads();
-      // the ring's new u, in place
+      // the ring's new s and u, in place
       // (every slot: slots past the tile's planes and outside the grid hold zeros)
 #pragma unroll
       for (int e0 = 0; e0 < kResTZ * kRing; e0 += kResBlock) {
         const int e = e0 + tid_l;
-        ring_u[e] = unew(ring_u[e], ring_w[e], ring_s[e]);
+        const float s_ = fmaf(b, ring_s[e], ring_w[e]);
+        ring_s[e] = s_;
+        ring_u[e] = fmaf(-a, s_, ring_u[e]);
       }
       __syncthreads();
       if (S.trace_detail) stamp();
       double acc[3] = {0.0, 0.0, 0.0};
-      // u, w/D, s/D on the tile's faces are published for the next iteration
-      // as each plane is done. The other bank, written here, was last read by
-      // the neighbours before the previous reduction, which this workgroup
-      // has passed.
-      float* uo_n = ub[cur ^ 1];
+      // w/D on the tile's faces is published for the next iteration as each
+      // plane is done. The other bank, written here, was last read by the
+      // neighbours before the previous reduction, which this workgroup has
+      // passed.
       float* wo_n = wb[cur ^ 1];
-      float* so_n = sb[cur ^ 1];
       // x += a p of this iteration, plane by plane; each plane's x is loaded
       // two planes ahead of its update (only this workgroup touches its x).
       // x and the published faces go through buffer accesses: a lane offset
@@ -672,7 +662,7 @@ __device__ __forceinline__ StepResult resident_step(const StepArgs<float>& S, co
       // inside the tile) out of range.
       constexpr int kXAhead = 2;
       const __amdgpu_buffer_rsrc_t rx = vec_rsrc(V.x, g.ng);
-      const __amdgpu_buffer_rsrc_t ru = vec_rsrc(uo_n, g.ng), rw = vec_rsrc(wo_n, g.ng), rs_ = vec_rsrc(so_n, g.ng);
+      const __amdgpu_buffer_rsrc_t rw = vec_rsrc(wo_n, g.ng);
       const unsigned vown = q.own ? 4u * (unsigned)col_l : kNoLane;
       const unsigned vedge = q.own && fedge ? 4u * (unsigned)col_l : kNoLane;
       // the compact x-edge columns of this iteration's bank: a lane offset on
@@ -697,35 +687,24 @@ __device__ __forceinline__ StepResult resident_step(const StepArgs<float>& S, co
                        acc[2] += rd * rd;
                        const unsigned vf = (z == 0 || z + 1 == ql.tzn) ? vown : vedge;
                        const int so = (z0_l + z) * pbytes;
-                       buf_st<kCpolSc1>(ru, vf, so, ur[z]);
                        buf_st<kCpolSc1>(rw, vf, so, wr[z]);
-                       buf_st<kCpolSc1>(rs_, vf, so, sr[z]);
-                       if (XF) {
-                         buf_st<kCpolSc1>(rxf, vxf, 32 * z, ur[z]);
-                         buf_st<kCpolSc1>(rxf, vxf, 4 * kXfCol + 32 * z, wr[z]);
-                         buf_st<kCpolSc1>(rxf, vxf, 8 * kXfCol + 32 * z, sr[z]);
-                       }
+                       if (XF) buf_st<kCpolSc1>(rxf, vxf, 4 * kXfCol + 32 * z, wr[z]);
                        const float xn = fmaf(a, pr[z], xq[z % (kXAhead + 1)]);
                        buf_st(rx, vown, so, xn);
                        if (z == 0) xtop = xn;
                      });
       stamp();
       if (S.trace_detail) stamp();
-      // the next iteration's halo rings start loading as soon as the
-      // neighbours have published this sweep's faces
+      // the next iteration's halo starts loading as soon as the neighbours
+      // have published this sweep's faces
       ok &= team_sum<float, 3, kResBlock, false>(S, rank, red, acc, rb, res_neighbours(g, tile, S.team, S.xcd_order, [&]() {
                               int tid_r = threadIdx.x, nxy_r = nxy;
                               asm volatile("" : "+v"(tid_r));
                               asm volatile("" : "+s"(nxy_r));
-                              if constexpr (XF) {
-                                ring_dma<G>(g, q, ring_u, uo_n, tid_r, nxy_r, xface_of(xf, S.team, 0, cur ^ 1), tile);
+                              if constexpr (XF)
                                 ring_dma<G>(g, q, ring_w, wo_n, tid_r, nxy_r, xface_of(xf, S.team, 1, cur ^ 1), tile);
-                                ring_dma<G>(g, q, ring_s, so_n, tid_r, nxy_r, xface_of(xf, S.team, 2, cur ^ 1), tile);
-                              } else {
-                                ring_dma<G>(g, q, ring_u, uo_n, tid_r, nxy_r);
+                              else
                                 ring_dma<G>(g, q, ring_w, wo_n, tid_r, nxy_r);
-                                ring_dma<G>(g, q, ring_s, so_n, tid_r, nxy_r);
-                              }
                             }));
       stamp();
       ++it;
