@@ -633,8 +633,10 @@ nh_status launch_step(nh_ctx* c, StepArgs<R>& S, int slot_ev, double* t_kernel) 
     NH_HIP(c, hipEventRecord(e0, c->stream));
   }
   if (sizeof(R) == 4 && c->resident)
-    NH_HIP(c, hipLaunchCooperativeKernel((const void*)nh::resident_step_kernel<64>, dim3(S.team),
-                                         dim3(nh::kResBlock), args, (unsigned)nh::kResLdsBytes, c->stream));
+    NH_HIP(c, hipLaunchCooperativeKernel(c->geom.TZ == nh::kResTZ && c->nz % nh::kResTZ == 0
+                                             ? (const void*)nh::resident_full_kernel<64>
+                                             : (const void*)nh::resident_step_kernel<64>,
+                                         dim3(S.team), dim3(nh::kResBlock), args, (unsigned)nh::kResLdsBytes, c->stream));
   else if (sizeof(R) == 4 && c->jac_tb) {
     // phase tags only grow between clears of the tagged buffers, so no stale word can match
     const unsigned phases = (unsigned)((S.jacobi_k + nh::kJacS - 1) / nh::kJacS);
@@ -1462,7 +1464,9 @@ nh_status nh_create(nh_ctx** out, int hip_device, void* hip_stream) {
   c->occ_f64 = std::max(1, o64);
   {
     int ro = 0;
-    if (hipFuncSetAttribute((const void*)nh::resident_step_kernel<64>,
+    if (hipFuncSetAttribute((const void*)nh::resident_full_kernel<64>,
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)nh::kResLdsBytes) == hipSuccess &&
+        hipFuncSetAttribute((const void*)nh::resident_step_kernel<64>,
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)nh::kResLdsBytes) == hipSuccess &&
         hipOccupancyMaxActiveBlocksPerMultiprocessor(&ro, (const void*)nh::resident_step_kernel<64>,
                                                      nh::kResBlock, nh::kResLdsBytes) == hipSuccess)

@@ -111,8 +111,16 @@ __device__ __forceinline__ void run_slice(const CJobRun& J, int2 m, JobProg* pro
     for (int d = 0; d < 3; ++d) ss->pc[d] = base + d < j0 ? J.it_out[slot_of(base + d)] : -1;
   }
   __syncthreads();
-  const StepArgs<float>& S = (const StepArgs<float>&)J.S;
+  // (each step reads the job anew: its fields, constant over the slice, would
+  // otherwise take the registers that the step needs; 84 of the streaming
+  // kernel's spilled to scratch)
+  const CJobRun* Jp = &J;
   while (true) {
+    asm volatile("" : "+s"(Jp));
+    const CJobRun& J = *Jp;
+    const StepArgs<float>& S = (const StepArgs<float>&)J.S;
+    auto pos = [&](int nn) { return J.mode == kForward ? nn - 1 : J.nsteps - nn; };
+    const bool fwd = J.mode == kForward;
     // (wave-uniform: the step's pointers below then live in scalar registers,
     // which leaves the step the vector registers of three planes per barrier)
     const int n = __builtin_amdgcn_readfirstlane(ss->n);
@@ -227,8 +235,8 @@ __global__ void __launch_bounds__(kResBlock, 1) batch_resident_kernel(const JobR
   if (m.x < 0) return;
   const CJobRun& J = *(const CJobRun*)(jobs + m.x);
   run_slice(J, m, prog, &ss, [&](const StepArgs<float>& S, const StepVar<float>& V) {
-    // three planes per barrier; the x-edge columns from the vectors (the
-    // compact copies would spill the slice's state)
+    // three planes per barrier; the x-edge columns from the vectors (jobs
+    // have no compact copies)
     return resident_step<64, 3>(S, V, m.y, dsm, true);
   });
 }
