@@ -1377,8 +1377,8 @@ nh_status do_tv(nh_ctx* c, const R* alpha, double eps, double weight, double* va
   if (!(eps > 0) || !std::isfinite(eps)) return fail(c, NH_EINVAL, "eps must be finite and > 0");
   if (!std::isfinite(weight)) return fail(c, NH_EINVAL, "weight must be finite");
   if (accumulate != 0 && accumulate != 1) return fail(c, NH_EINVAL, "accumulate must be 0 or 1");
-  const long long ng = (long long)c->nx * c->ny * c->nz;
-  const int blocks = (int)std::min<long long>((ng + nh::kTvBlock - 1) / nh::kTvBlock, nh::kTvMaxBlocks);
+  const nh::TvPlan plan = nh::tv_plan(c->nx, c->ny, c->nz, c->num_cu);
+  const int blocks = plan.blocks;
   double* partial = nullptr;
   if (noalloc) {
     if (!c->scratch) return fail(c, NH_ESTATE, "the device scratch array was not resolved");
@@ -1396,7 +1396,7 @@ nh_status do_tv(nh_ctx* c, const R* alpha, double eps, double weight, double* va
   A.ny = c->ny;
   A.nz = c->nz;
   A.nxy = (long long)c->nx * c->ny;
-  A.ng = ng;
+  A.P = plan;
   A.ix2 = (R)(1.0 / (c->hx * c->hx));
   A.iy2 = (R)(1.0 / (c->hy * c->hy));
   A.iz2 = (R)(1.0 / (c->hz * c->hz));
@@ -1405,9 +1405,12 @@ nh_status do_tv(nh_ctx* c, const R* alpha, double eps, double weight, double* va
   A.grad = grad;
   A.accumulate = accumulate;
   A.partial = partial;
-  hipLaunchKernelGGL(nh::tv_kernel<R>, dim3(blocks), dim3(nh::kTvBlock), 0, c->stream, A);
+  if (plan.rows == 1)
+    hipLaunchKernelGGL((nh::tv_kernel<R, 1>), dim3(blocks), dim3(nh::kTvBlock), 0, c->stream, A);
+  else
+    hipLaunchKernelGGL((nh::tv_kernel<R, nh::kTvRows>), dim3(blocks), dim3(nh::kTvBlock), 0, c->stream, A);
   NH_HIP(c, hipGetLastError());
-  hipLaunchKernelGGL(nh::tv_finish_kernel, dim3(1), dim3(nh::kTvBlock), 0, c->stream, (const double*)A.partial,
+  hipLaunchKernelGGL(nh::tv_finish_kernel, dim3(1), dim3(nh::kTvFinish), 0, c->stream, (const double*)A.partial,
                      blocks, A.scale, value);
   NH_HIP(c, hipGetLastError());
   if (!noalloc) NH_HIP(c, hipStreamSynchronize(c->stream));
