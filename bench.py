@@ -392,10 +392,13 @@ def main():
     iters = it_f + it_a + it_r
     st = solver.stats()
     roof = None
-    if st["resident"]:
-        kname = "nh::resident_step_kernel<64>"
+    if st["launches_fwd"] < st["fwd_steps"] and not st["jacobi_blocked"]:
+        kname = "nh::brick_steps_kernel"     # several steps per launch
+    elif st["resident"]:
+        full = st["tile_z"] == 32 and w.nz % 32 == 0
+        kname = "nh::resident_full_kernel<64>" if full else "nh::resident_step_kernel<64>"
     elif st["jacobi_blocked"]:
-        kname = "nh::jacobi_steps_kernel<8>"
+        kname = f"nh::jacobi_steps_kernel<{st['tile_y']}>" if w.nz <= 16 else "nh::jacobi_deep_kernel"
     else:
         kname = "nh::step_kernel<float>" if w.precision == "f32" else "nh::step_kernel<double>"
     if not args.no_profile and (tk_f + tk_a) > 0:

@@ -89,8 +89,9 @@ typedef struct {
     int team_blocks;            /* workgroups cooperating on one step */
     int block_threads;          /* threads per workgroup */
     int tile_x, tile_y, tile_z; /* tile extents of the stencil kernels */
-    int resident;               /* 1: the register-resident step kernel runs this grid */
-    int resident_occupancy;     /* workgroups of that kernel that fit one CU (0: unusable) */
+    int resident;               /* 1: FP32 with zero-flux walls and the CG state in registers, on the
+                                   register-resident step kernel or the brick kernel (several steps a launch) */
+    int resident_occupancy;     /* workgroups of the former that fit one CU (0: unusable) */
     int jacobi_blocked;         /* 1: fixed-K steps run on the temporally blocked kernel */
 } nh_stats;
 
@@ -119,8 +120,8 @@ nh_status nh_set_solver(nh_ctx *ctx, double rtol, int max_iter, int checkpoint_e
  * coefficient h of the back-face condition n.(alpha grad T) = -h T on the
  * plane k = nz-1: its rows carry the diagonal sink beta = h / hz, which does
  * not depend on alpha. Default 0, 0: zero flux on all six faces. The plane
- * k = 0 stays adiabatic. Grids with either closure run on the streaming step
- * kernel. Frees the saved forward state. */
+ * k = 0 stays adiabatic. Grids with either closure that the brick kernel does not
+ * hold run on the streaming step kernel (nh_set_cg_variant). Frees the saved forward state. */
 nh_status nh_set_boundary(nh_ctx *ctx, int periodic_xy, double robin_h);
 
 /* Inner solver. k = 0 (default): Jacobi-preconditioned CG to rtol. k > 0:
@@ -240,8 +241,11 @@ nh_status nh_set_launch(nh_ctx *ctx, int team_blocks_max, int tile_z, int profil
  * r.z and |r|^2); 1 = the single-reduction form of Chronopoulos and Gear,
  * which carries A u and A p as extra vectors so that r.z, u.Au and |r|^2 are
  * reduced together once per iteration; 2 (default) = form 1 with the whole CG
- * state of a tile in registers where the grid fits on the device (FP32,
- * zero-flux walls), else form 1. A variant other than 0 resets the
+ * state of a tile in registers where the grid fits on the device: in bricks
+ * of at most 4096 cells with the operator in registers too (FP32 to about a
+ * million cells and FP64 to about half of that, any closure, automatic
+ * tiling), else in tiles of 64 x 8 x 32 cells (FP32, zero-flux walls), else
+ * form 1. A variant other than 0 resets the
  * preconditioner to Jacobi. Frees the saved forward. */
 nh_status nh_set_cg_variant(nh_ctx *ctx, int variant);
 

@@ -2,7 +2,8 @@
 //
 // The runtime owns one HIP stream per context, the context's device
 // workspaces and the saved forward state, and drives the time loop: one
-// cooperative launch of nh::step_kernel per implicit-Euler step (Sec. 4.2),
+// cooperative launch per implicit-Euler step (Sec. 4.2) -- or per twelve of
+// them, for grids that the brick or the blocked fixed-K kernel holds --
 // forward in time for the state and backward in time for the adjoint
 // (Sec. 4.3). With checkpointing every k steps the adjoint recomputes each
 // k-step segment from its checkpoint before sweeping it backwards; the
@@ -178,7 +179,7 @@ struct nh_ctx {
   int cheb_m = 1;                            // preconditioner: 1 Jacobi, >= 2 Chebyshev polynomial (variant 0)
   double cheb_dmax = 1.0;                    // max D of the saved forward's operator (Chebyshev interval)
   Buf dmaxb;                                 // device result of nh::dmax_kernel
-  bool resident = false;                     // the current plan uses nh::resident_step_kernel
+  bool resident = false;                     // the current plan uses nh::resident_step_kernel or resident_full_kernel
   bool jac_tb = false;                       // the current plan uses the blocked fixed-K kernels
   int jac_iy = 0;                            //   on interior tiles of this many rows
   int jtx = 0, jty = 0;                      //   with this many interior tiles per axis
