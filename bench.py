@@ -261,7 +261,7 @@ def long_section(dev, nsteps: int, k: int) -> dict:
                     "peak_workspace_gb": st["peak_workspace_bytes"] / 1e9,
                     "cg_iters": {"fwd": st["fwd_iters"], "adj": st["adj_iters"],
                                  "recompute": st["recompute_iters"]},
-                    "kernel": "nh::resident_step_kernel<64>" if st["resident"] else "nh::step_kernel<float>"}
+                    "kernel": "nh::resident_full_kernel<64>" if st["resident"] else "nh::step_kernel<float>"}
         print(f"[bench] long {key}: {el:.2f} s per pass, peak workspace "
               f"{st['peak_workspace_bytes'] / 1e9:.1f} GB", file=sys.stderr, flush=True)
         s.close()
