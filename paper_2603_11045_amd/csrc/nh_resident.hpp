@@ -648,10 +648,24 @@ __device__ __forceinline__ StepResult resident_step(const StepArgs<float>& S, co
     float* ring_u = lring;
     float* ring_w = lring + kResTZ * kRing;
     float* ring_s = lring + 2 * kResTZ * kRing;
+    // w/D below and above the tile is loaded with the ring, inside the reduction
+    // (six jobs through the server: 82.8 to 80.7 ms), or, where no register is
+    // left for it there (FULL: one would spill), right after
+    float zwl = 0.f, zwh = 0.f;
+    auto load_z = [&](const float* w) {
+      int nxy_z = nxy, col_z = q.col;
+      asm volatile("" : "+s"(nxy_z));
+      asm volatile("" : "+v"(col_z));
+      const __amdgpu_buffer_rsrc_t r = vec_rsrc(w, g.ng);
+      const unsigned vo = q.own ? 4u * (unsigned)col_z : kNoLane;
+      zwl = buf_ld<kCpolSc1>(r, q.bot_z ? vo : kNoLane, 4 * (T.z0 - 1) * nxy_z);
+      zwh = buf_ld<kCpolSc1>(r, q.top_z ? vo : kNoLane, 4 * T.z1 * nxy_z);
+    };
     ok &= team_sum<float, 1, kResBlock, false>(S, rank, red, acc1, rb, res_neighbours(g, tile, S.team, S.xcd_order, [&]() {
                             int tid_l = threadIdx.x, nxy_l = nxy;
                             asm volatile("" : "+v"(tid_l));
                             asm volatile("" : "+s"(nxy_l));
+                            if constexpr (!FULL) load_z(wb[0]);
                             if constexpr (XF)
                               ring_dma<G>(g, q, ring_w, wb[0], tid_l, nxy_l, xface_of(xf, S.team, 1, 0), tile);
                             else
@@ -677,15 +691,16 @@ __device__ __forceinline__ StepResult resident_step(const StepArgs<float>& S, co
       if constexpr (!FULL) asm volatile("" : "+s"(ql.tzn));
       asm volatile("" : "+s"(z0_l));
       const float a = (float)a_cg, b = (float)b_cg;
-      // the neighbours' published w/D on the tile's ring is on its way to LDS
-      // already (started inside the last reduction); the values below and above
-      // the tile are loaded now and land while the registers are updated
-      const float* wo = wb[cur];
+      // the neighbours' published w/D -- the ring's to LDS, the values below and
+      // above the tile to registers -- is on its way
+      if constexpr (FULL) {
+        const float* wo = wb[cur];
+        zwl = zwh = 0.f;
+        if (q.own && q.bot_z) zwl = ld_dev(wo + col_l + (T.z0 - 1) * nxy_l);
+        if (q.own && q.top_z) zwh = ld_dev(wo + col_l + T.z1 * nxy_l);
+      }
       int tid_l = threadIdx.x;
       asm volatile("" : "+v"(tid_l));
-      float zwl = 0.f, zwh = 0.f;
-      if (q.own && q.bot_z) zwl = ld_dev(wo + col_l + (T.z0 - 1) * nxy_l);
-      if (q.own && q.top_z) zwh = ld_dev(wo + col_l + T.z1 * nxy_l);
       // elementwise updates: s = w + b s, p = u + b p, u -= a s in registers
       // (x += a p follows plane by plane in the sweep, where its memory
       // traffic hides behind the stencil's arithmetic). In the first
@@ -775,6 +790,7 @@ __device__ __forceinline__ StepResult resident_step(const StepArgs<float>& S, co
                               int tid_r = threadIdx.x, nxy_r = nxy;
                               asm volatile("" : "+v"(tid_r));
                               asm volatile("" : "+s"(nxy_r));
+                              if constexpr (!FULL) load_z(wo_n);
                               if constexpr (XF)
                                 ring_dma<G>(g, q, ring_w, wo_n, tid_r, nxy_r, xface_of(xf, S.team, 1, cur ^ 1), tile);
                               else
