@@ -546,11 +546,10 @@ nh_status queue_brick(nh_ctx* c, const StepArgs<R>& S, int slot_ev) {
   }
   q.tab.v[n] = nh::step_var(S);
   q.iters[n] = S.out_iters;
-  for (int d = 0; d < 3; ++d) {
-    q.tab.lg[n][d] = -1;
-    for (int j = 0; j < n && S.gmode < 0; ++j)
-      if (q.iters[j] == S.gi + S.gp[d]) q.tab.lg[n][d] = (signed char)j;
-  }
+  q.tab.here[n] = 0;
+  for (int d = 0; d < 3 && S.gmode < 0; ++d)
+    for (int j = 0; j < n; ++j)
+      if (q.iters[j] == S.gi + S.gp[d]) q.tab.here[n] |= (unsigned char)(1 << d);
   ++q.tab.count;
   // (a launch's reductions stay below 2^24 epochs)
   if (q.tab.count == nh::kBrickSteps || (long long)(q.tab.count + 1) * ((long long)S.max_iter + 8) >= (1 << 24))

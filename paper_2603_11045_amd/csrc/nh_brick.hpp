@@ -40,12 +40,12 @@ namespace nh {
 constexpr int kBrickSteps = 12;             // steps per launch (their fields travel as kernel arguments)
 
 // The steps of a launch. Where a step's adaptive initial guess compares the
-// iteration counts of probe steps in the same launch, lg holds their positions
-// in it (-1: an earlier launch, read from gi).
+// iteration counts of probe steps, bit d of here says that the probe of order d
+// is an earlier step of this launch (else its count is read from gi).
 template <typename R>
 struct BrickSteps {
   StepVar<R> v[kBrickSteps];
-  signed char lg[kBrickSteps][4];
+  unsigned char here[kBrickSteps];
   int count;
 };
 
@@ -118,7 +118,6 @@ __global__ void __launch_bounds__(NT, 1) brick_steps_kernel(StepArgs<R> S, Brick
   constexpr unsigned SZ = sizeof(R);
   __shared__ R lu[ZC * PLX];
   __shared__ RedBuf rb;
-  __shared__ int its[kBrickSteps];
   const Geom& g = S.g;
   const int tid = threadIdx.x, rank = blockIdx.x;
   const Tile T = tile_of(g, rank);
@@ -282,22 +281,23 @@ __global__ void __launch_bounds__(NT, 1) brick_steps_kernel(StepArgs<R> S, Brick
 
   unsigned long long red = tab.v[0].epoch_base;
   bool ok = true;
+  // iteration counts of this launch's latest probe of each order. Every wave has
+  // them from the team reductions, so a step needs nothing of the step before it
+  // from LDS (there is no barrier between two forward steps).
+  int pc0 = 0, pc1 = 0, pc2 = 0;
   __syncthreads();
   for (int st = 0; st < tab.count; ++st) {
     const StepVar<R>& V = tab.v[st];
-    // ---- initial guess (guess_order with the counts of this launch's probes from LDS)
+    // ---- initial guess (guess_order with the counts of this launch's probes)
     int order = V.gmode;
     if (order < 0) {
-      int c[3];
-#pragma unroll
-      for (int d = 0; d < 3; ++d) {
-        const int l = tab.lg[st][d];
-        c[d] = l >= 0 ? its[l] : V.gi[V.gp[d]];
-      }
+      const int here = tab.here[st];
+      const int c0 = here & 1 ? pc0 : V.gi[V.gp[0]], c1 = here & 2 ? pc1 : V.gi[V.gp[1]],
+                c2 = here & 4 ? pc2 : V.gi[V.gp[2]];
       order = 2;
-      int best = c[2];
-      if (c[1] < best) { order = 1; best = c[1]; }
-      if (c[0] < best) order = 0;
+      int best = c2;
+      if (c1 < best) { order = 1; best = c1; }
+      if (c0 < best) order = 0;
     }
     if (order == 3) order = V.xprev && V.xprev2 ? 3 : 0;
     else if (!V.xprev || !V.xprev2) order = 0;
@@ -466,13 +466,16 @@ __global__ void __launch_bounds__(NT, 1) brick_steps_kernel(StepArgs<R> S, Brick
     }
     if (own && V.surf_out && T.z0 == 0) V.surf_out[gx + g.nx * gy] = S.mode == kForward ? x[0] : V.surf_scale * x[0];
     const double relres = bb > 0.0 ? sqrt(rr / bb) : 0.0;
-    if (tid == 0) {
-      its[st] = it;
-      if (rank == 0 && V.out_iters) {
-        V.out_iters[0] = it;
-        V.out_relres[0] = relres;
-        V.out_status[0] = status;
-      }
+    if (tid == 0 && rank == 0 && V.out_iters) {
+      V.out_iters[0] = it;
+      V.out_relres[0] = relres;
+      V.out_status[0] = status;
+    }
+    {
+      const int n = __builtin_amdgcn_readfirstlane(it);
+      if (V.gmode == 0) pc0 = n;
+      if (V.gmode == 1) pc1 = n;
+      if (V.gmode == 2) pc2 = n;
     }
     if (!ok) return;                        // a wait timed out: every workgroup leaves within its own time limit
     if (S.mode == kAdjoint && V.T_grad) {
