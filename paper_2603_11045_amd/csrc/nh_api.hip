@@ -186,6 +186,7 @@ struct nh_ctx {
   int brick_nt = 0, brick_zc = 0;            // the current plan uses nh::brick_steps_kernel (0: not) with
                                              //   this many threads and cells per thread
   unsigned long long launch_ctr = 0;         // makes every launch's reduction epochs unique
+  unsigned long long tag_round = 0;          // the round of tags that slots and halo were last cleared for
   size_t ws_bytes = 0, ws_peak = 0;
 
   Geom geom{};
@@ -500,14 +501,18 @@ int occupancy(nh_ctx* c) {
 }
 
 // Make the reduction slots ready for a launch with epochs from epoch_base on.
-// Tags are the low 32 bits of the epochs, which repeat every 256 launches: the
-// slots are zeroed when a launch starts a new round of 256, so no stale word
-// can carry the tag a reader waits for.
+// Tags are the low 32 bits of the epochs, which repeat every 256 launch numbers:
+// the slots are zeroed before the first launch of each round of 256, whichever
+// number it has (a launch of several steps passes over theirs), so no stale
+// word can carry the tag a reader waits for, also where another grid, precision
+// or solver of this context has left the words as they are for a while.
 nh_status prepare_slots(nh_ctx* c, unsigned long long epoch_base) {
-  if (((epoch_base >> 24) & 0xFF) != 0) return NH_OK;
+  const unsigned long long round = epoch_base >> 32;
+  if (round == c->tag_round) return NH_OK;
   if (c->halo.p)                             // the brick kernel's halo words carry the same tags
     NH_TRY(fill<unsigned long long>(c, (unsigned long long*)c->halo.p, (long long)(c->halo.bytes / 8), 0ull));
   NH_TRY(fill<unsigned long long>(c, (unsigned long long*)c->slots.p, (long long)(c->slots.bytes / 8), 0ull));
+  c->tag_round = round;
   return NH_OK;
 }
 

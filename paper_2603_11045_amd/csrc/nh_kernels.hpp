@@ -262,8 +262,9 @@ __device__ __forceinline__ void wave_sums(double (&v)[NV]) {
 // values and their validity in one load round trip (16 bytes a load; each
 // 8-byte word carries its own tag), and the writer waits for nothing between
 // its words. Tags are unique between clears of the slots: an epoch is
-// (launch << 24) + k with k < 2^24 reductions per launch, and the host zeroes
-// the slots every 256 launches (tag 0 is never used). Slots alternate between
+// (number << 24) + k with k < 2^24 reductions per launch, numbers grow from launch
+// to launch, and the host zeroes the slots before the first launch of each round
+// of 256 numbers (tag 0 is never used). Slots alternate between
 // two banks by epoch parity: a workgroup can be at most one reduction ahead of
 // the slowest reader (the next reduction needs every workgroup's slot), so a
 // bank is never rewritten while still read. Every value another workgroup reads
