@@ -251,7 +251,14 @@ nh_status ensure(nh_ctx* c, Buf& b, size_t bytes) {
   return NH_OK;
 }
 
+// Forget the steps that wait to be launched (a call that failed left them).
+void drop_queued(nh_ctx* c) {
+  c->jq.count = c->bq32.tab.count = c->bq64.tab.count = 0;
+  c->jq_ev = c->bq32.ev = c->bq64.ev = -1;
+}
+
 void drop_forward(nh_ctx* c) {
+  drop_queued(c);
   c->saved_prec = 0;
   c->saved_nsteps = 0;
   release(c, c->traj);
@@ -519,8 +526,7 @@ nh_status prepare_slots(nh_ctx* c, unsigned long long epoch_base) {
 // Launch the queued brick steps as one launch, timed with the event pair of
 // the first of them.
 template <typename R>
-nh_status flush_brick(nh_ctx* c, BrickQueue<R>& q) {
-  if (q.tab.count == 0) return NH_OK;
+nh_status launch_brick(nh_ctx* c, BrickQueue<R>& q) {
   NH_TRY(prepare_slots(c, q.tab.v[0].epoch_base));
   const bool timed = c->profile && q.ev >= 0;
   if (timed) NH_HIP(c, hipEventRecord(c->ev[2 * q.ev], c->stream));
@@ -532,9 +538,16 @@ nh_status flush_brick(nh_ctx* c, BrickQueue<R>& q) {
     c->ev_rec[q.ev] = 1;
   }
   ++c->kernel_launches;
-  q.tab.count = 0;
-  q.ev = -1;
   return NH_OK;
+}
+
+template <typename R>
+nh_status flush_brick(nh_ctx* c, BrickQueue<R>& q) {
+  if (q.tab.count == 0) return NH_OK;
+  const nh_status s = launch_brick(c, q);
+  q.tab.count = 0;                           // launched, or lost with the call that failed
+  q.ev = -1;
+  return s;
 }
 
 // Queue one brick step; steps of one sweep share everything but their StepVar fields.
@@ -564,10 +577,7 @@ nh_status queue_brick(nh_ctx* c, const StepArgs<R>& S, int slot_ev) {
 
 // Launch the queued steps of the blocked fixed-K kernel as one launch, timed
 // with the event pair of the first of them.
-nh_status flush_steps(nh_ctx* c) {
-  NH_TRY(flush_brick(c, c->bq32));
-  NH_TRY(flush_brick(c, c->bq64));
-  if (c->jq.count == 0) return NH_OK;
+nh_status launch_jacobi(nh_ctx* c) {
   NH_TRY(prepare_slots(c, c->jq_epoch));
   hipEvent_t e0 = nullptr, e1 = nullptr;
   if (c->profile && c->jq_ev >= 0) {
@@ -583,9 +593,18 @@ nh_status flush_steps(nh_ctx* c) {
     c->ev_rec[c->jq_ev] = 1;
   }
   ++c->kernel_launches;
-  c->jq.count = 0;
-  c->jq_ev = -1;
   return NH_OK;
+}
+
+// Launch whatever is queued.
+nh_status flush_steps(nh_ctx* c) {
+  NH_TRY(flush_brick(c, c->bq32));
+  NH_TRY(flush_brick(c, c->bq64));
+  if (c->jq.count == 0) return NH_OK;
+  const nh_status s = launch_jacobi(c);
+  c->jq.count = 0;                           // launched, or lost with the call that failed
+  c->jq_ev = -1;
+  return s;
 }
 
 // Queue one step of the blocked fixed-K kernel; steps of one sweep share
@@ -1194,6 +1213,7 @@ nh_status do_adjoint(nh_ctx* c, const R* gsurf, double* G, R* dq, R* dT0) {
   if (!gsurf || !G) return fail(c, NH_EINVAL, "null pointer argument");
   if (c->saved_prec != (int)sizeof(R))
     return fail(c, NH_ESTATE, "no saved forward of this precision (call the matching nh_forward first)");
+  drop_queued(c);
   const Geom& g = c->geom;
   const int N = c->saved_nsteps, k = c->ckpt_every;
   const double dt = c->saved_dt;

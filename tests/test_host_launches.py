@@ -94,3 +94,40 @@ lines = launches(CLEAR, *STEPS)              # in one go, before a step
 first = lines.index(cleared[0])
 assert lines[first:first + {words}] == cleared and CLEAR not in lines[first + {words}]
 """)
+
+
+@pytest.mark.parametrize("setup", ["grid(16, 16, 8)", "grid(16, 16, 8); double = True",
+                                   "grid(64, 64, 16); lib.nh_set_jacobi_sweeps(ctx, 10)"],
+                         ids=["bricks", "bricks-f64", "fixed-k"])
+@pytest.mark.parametrize("after", ["", "grid(200, 160, 64)", "lib.nh_set_launch(ctx, 0, 4, 0)", "double = not double"],
+                         ids=["same-plan", "other-grid", "streaming", "other-precision"])
+def test_a_failed_launch_leaves_no_steps_for_the_next_call(run, setup, after):
+    """The steps of a launch that failed are gone with it: the next call launches its
+    own alone (the old ones point into a trajectory that has been freed)."""
+    run(f"""
+double = False
+{setup}
+for steps, failing in ((5, 1), (12, 1), (30, 2)):
+    hip.host_hip_fail_cooperative(failing)
+    assert forward(steps, double) == -6
+    before = double
+    {after or "pass"}
+    hip.host_hip_reset()
+    assert forward(1, double) == 0
+    assert len(launches(*STEPS)) == 1, launches(*STEPS)
+    double = before
+    lib.nh_set_launch(ctx, 0, 0, 0)
+    {setup.replace("double = True", "pass")}
+""")
+
+
+def test_a_failed_launch_of_an_adjoint_leaves_no_steps(run):
+    run("""
+grid(16, 16, 8)
+assert forward(5) == 0
+hip.host_hip_fail_cooperative(1)
+assert adjoint(5) == -6
+hip.host_hip_reset()
+assert adjoint(5) == 0                       # the forward is still saved
+assert len(launches(*STEPS)) == 1, launches(*STEPS)
+""")
