@@ -61,17 +61,17 @@ inline TvPlan tv_plan(int nx, int ny, int nz, int cus) {
   P.lx = nx > 32 ? 6 : (nx > 16 ? 5 : 4);
   const int groups = 64 >> P.lx;
   const long long want = (long long)cus * 4 * kTvWaves;
-  P.ux = (nx + (1 << P.lx) - 1) >> P.lx;
+  P.ux = (int)(((long long)nx + (1 << P.lx) - 1) >> P.lx);
   P.rows = kTvRows;
-  P.uy = (ny + groups * P.rows - 1) / (groups * P.rows);
+  P.uy = (int)(((long long)ny + groups * P.rows - 1) / (groups * P.rows));
   if ((long long)P.ux * P.uy * nz < want) {
     P.rows = 1;
-    P.uy = (ny + groups - 1) / groups;
+    P.uy = (int)(((long long)ny + groups - 1) / groups);
   }
   const long long cols = (long long)P.ux * P.uy;
   P.pz = 64 / (groups * P.rows);
-  while (P.pz > 1 && cols * ((nz + P.pz - 1) / P.pz) < want) P.pz >>= 1;
-  P.uz = (nz + P.pz - 1) / P.pz;
+  while (P.pz > 1 && cols * (((long long)nz + P.pz - 1) / P.pz) < want) P.pz >>= 1;
+  P.uz = (int)(((long long)nz + P.pz - 1) / P.pz);
   P.units = (int)(cols * P.uz);
   P.blocks = (int)std::min<long long>((P.units + kTvBlock / 64 - 1) / (kTvBlock / 64), kTvMaxBlocks);
   return P;
@@ -112,9 +112,11 @@ __device__ __forceinline__ R tv_term(const TvArgs<R>& A, R ap, R ax, R ay, R dz,
   return t;
 }
 
-// row j0 + s of the wrapping y axis (s >= -1; past the row after the last: any row)
-__device__ __forceinline__ int tv_row(int j, int ny) {
-  j = j < 0 ? ny - 1 : j;
+// Row j of the wrapping y axis (unsigned: -1 is the row before the first; past
+// the row after the last: any row). Offsets are 64-bit, an x-y plane may hold
+// 2^31 cells and more; indices that run past an axis' end are unsigned.
+__device__ __forceinline__ unsigned tv_row(unsigned j, unsigned ny) {
+  j = j == ~0u ? ny - 1 : j;
   j = j >= ny ? j - ny : j;
   return j >= ny ? 0 : j;
 }
@@ -129,26 +131,28 @@ __global__ void __launch_bounds__(kTvBlock) tv_kernel(TvArgs<R> A) {
   for (int u = (int)blockIdx.x * (kTvBlock / 64) + wave; u < A.P.units; u += (int)gridDim.x * (kTvBlock / 64)) {
     const int uxy = A.P.ux * A.P.uy;
     const int uz = u / uxy, uc = u - uz * uxy, uy = uc / A.P.ux, ux = uc - uy * A.P.ux;
-    const int x0 = ux << lx, k0 = uz * A.P.pz, k1 = min(A.nz, k0 + A.P.pz);
-    const int j0 = (uy * groups + grp) * K;
-    const bool xin = x0 + tx < A.nx;
-    const int i = xin ? x0 + tx : 0, ip = i + 1 < A.nx ? i + 1 : 0;
-    int row[K + 2];                         // offsets of rows j0 - 1 .. j0 + K
+    const unsigned nx = A.nx, ny = A.ny, nz = A.nz;
+    const unsigned x0 = (unsigned)ux << lx, k0 = (unsigned)uz * A.P.pz, k1 = min(nz, k0 + A.P.pz);
+    const unsigned j0 = ((unsigned)uy * groups + grp) * K;
+    const bool xin = x0 + tx < nx;
+    const unsigned i = xin ? x0 + tx : 0, ip = i + 1 < nx ? i + 1 : 0;
+    long long row[K + 2];                   // offsets of rows j0 - 1 .. j0 + K
 #pragma unroll
-    for (int s = 0; s < K + 2; ++s) row[s] = A.nx * tv_row(j0 - 1 + s, A.ny);
+    for (int s = 0; s < K + 2; ++s) row[s] = (long long)nx * tv_row(j0 - 1 + s, ny);
 
     // the column before the wave's first, all its rows and planes: lane
     // (plane * groups + group) * K + row computes that cell's x weight
     TvTerm<R> hx{R(0), R(0), R(0), R(0)};
     {
-      const int r = lane % K, hg = lane / K % groups, hk = k0 + lane / (K * groups);
-      const int hj = (uy * groups + hg) * K + r;
-      if (hk < k1 && hj < A.ny) {
+      const unsigned r = lane % K, hg = lane / K % groups, hk = k0 + lane / (K * groups);
+      const unsigned hj = ((unsigned)uy * groups + hg) * K + r;
+      if (hk < k1 && hj < ny) {
         const R* pk = A.alpha + (long long)hk * A.nxy;
-        const int ho = A.nx * hj, hi = x0 > 0 ? x0 - 1 : A.nx - 1;
+        const long long ho = (long long)nx * hj;
+        const unsigned hi = x0 > 0 ? x0 - 1 : nx - 1;
         const R ap = pk[ho + hi];
-        const R dz = hk + 1 < A.nz ? pk[A.nxy + ho + hi] - ap : R(0);
-        tv_term(A, ap, pk[ho + x0], pk[A.nx * tv_row(hj + 1, A.ny) + hi], dz, hx);
+        const R dz = hk + 1 < nz ? pk[A.nxy + ho + hi] - ap : R(0);
+        tv_term(A, ap, pk[ho + x0], pk[(long long)nx * tv_row(hj + 1, ny) + hi], dz, hx);
       }
     }
 
@@ -176,8 +180,8 @@ __global__ void __launch_bounds__(kTvBlock) tv_kernel(TvArgs<R> A) {
         rtb[r] = o.rt;
       }
     }
-    for (int k = k0; k < k1; ++k) {
-      const bool last = k + 1 == A.nz;
+    for (unsigned k = k0; k < k1; ++k) {
+      const bool last = k + 1 == nz;
       const R* pn = A.alpha + (long long)(last ? k : k + 1) * A.nxy;
       double* gk = A.grad + (long long)k * A.nxy;
       R an[K + 2], anx[K + 1];
@@ -186,7 +190,7 @@ __global__ void __launch_bounds__(kTvBlock) tv_kernel(TvArgs<R> A) {
       for (int s = 0; s < K + 2; ++s) an[s] = pn[row[s] + i];
       if (A.accumulate) {
 #pragma unroll
-        for (int r = 0; r < K; ++r) g0[r] = xin && j0 + r < A.ny ? gk[row[r + 1] + i] : 0.0;
+        for (int r = 0; r < K; ++r) g0[r] = xin && j0 + r < ny ? gk[row[r + 1] + i] : 0.0;
       }
 #pragma unroll
       for (int s = 0; s < K + 1; ++s) anx[s] = pn[row[s] + ip];
@@ -196,7 +200,7 @@ __global__ void __launch_bounds__(kTvBlock) tv_kernel(TvArgs<R> A) {
         TvTerm<R> o;
         const R t = tv_term(A, av[s], ax[s], av[s + 1], last ? R(0) : an[s] - av[s], o);
         if (s > 0) {
-          const int r = s - 1, hl = ((k - k0) * groups + grp) * K + r;
+          const int r = s - 1, hl = ((int)(k - k0) * groups + grp) * K + r;
           // the cell is the +x neighbour of the one before it
           const R cxl = __shfl_up(o.cx, 1, 64), rtl = __shfl_up(o.rt, 1, 64);
           const R cxh = __shfl(hx.cx, hl, 64), rth = __shfl(hx.rt, hl, 64);
@@ -204,7 +208,7 @@ __global__ void __launch_bounds__(kTvBlock) tv_kernel(TvArgs<R> A) {
           g = fma_r(tx > 0 ? cxl : cxh, tx > 0 ? rtl : rth, g);
           g = fma_r(cyb, rty, g);
           if (k > 0) g = fma_r(czb[r], rtb[r], g);
-          if (xin && j0 + r < A.ny) {
+          if (xin && j0 + r < ny) {
             const double v = mul_rn(A.scale, (double)g);   // (not fused: the same gradient, added or not)
             gk[row[s] + i] = A.accumulate ? add_rn(g0[r], v) : v;
             tsum += (double)t;
