@@ -1430,7 +1430,9 @@ nh_status do_tv(nh_ctx* c, const R* alpha, double eps, double weight, double* va
   A.grad = grad;
   A.accumulate = accumulate;
   A.partial = partial;
-  if (plan.rows == 1)
+  if (plan.rows == 0)
+    hipLaunchKernelGGL(nh::tv_cell_kernel<R>, dim3(blocks), dim3(nh::kTvBlock), 0, c->stream, A);
+  else if (plan.rows == 1)
     hipLaunchKernelGGL((nh::tv_kernel<R, 1>), dim3(blocks), dim3(nh::kTvBlock), 0, c->stream, A);
   else
     hipLaunchKernelGGL((nh::tv_kernel<R, nh::kTvRows>), dim3(blocks), dim3(nh::kTvBlock), 0, c->stream, A);

@@ -10,19 +10,20 @@
 //
 // A term is some 40 instructions (a square root and a division, both
 // correctly rounded), and with the four terms of every cell computed by its
-// own thread, at 64-bit indices, the instructions took longer than the memory
-// traffic. So each term is computed once wherever a wave can hand it on: a
+// own thread the instructions of a large grid take longer than the memory
+// traffic. So there each term is computed once wherever a wave can hand it on: a
 // lane walks a few rows of one column up a few planes, keeps the row's y
 // weight for the next row and the plane's z weights for the next plane, and
 // takes the x weight from the lane beside it. What a wave computes besides
 // its cells is the row before its first, the plane below its first and the
 // column before its first, the last for all its rows and planes in one go, a
-// lane each. No LDS, no barrier: the waves are independent.
+// lane each. No LDS, no barrier: the waves are independent. (Small and thin
+// grids keep a thread per cell, see tv_plan.)
 //
-// On 256 x 256 x 64 (FP32, added to a gradient: 84 MB) the call took 65.5 us
-// and now takes 47, of which some 31 are its launches, its synchronisation
-// and the value's way to the host; on 512 x 512 x 64 (336 MB) 157 and now
-// 100.7 us, near 5 TB/s. What is left of the kernel is memory traffic.
+// On 256 x 256 x 64 (FP32, added to a gradient: 84 MB, which stay in the
+// last-level cache from call to call) the entry point took 51 us and now takes
+// 31, some 15 of them two launches and a synchronisation; on 512 x 512 x 64
+// (336 MB) 144 and now 85 us. What is left of the kernel is memory traffic.
 //
 // The workgroup's partial sum of t goes to its own slot; tv_finish_kernel sums
 // the slots in a fixed order, so the value is deterministic.
@@ -40,6 +41,8 @@ constexpr int kTvBlock = 256;
 constexpr int kTvMaxBlocks = 4096;
 constexpr int kTvFinish = 512;
 constexpr int kTvRows = 4;                  // rows of one column per lane, on grids large enough
+constexpr int kTvThin = 100;                // a thread per cell up to this many columns,
+constexpr int kTvCellWaves = 5;             //   and up to this many waves per SIMD of such threads
 constexpr int kTvWaves = 4;                 // waves per SIMD that a plan aims at
 
 // How waves cover the grid: lanes of 1 << lx columns, 64 >> lx groups of
@@ -50,21 +53,39 @@ struct TvPlan {
   int units, blocks;
 };
 
-// Narrow grids fold rows into the lanes. A unit of one row and one plane
-// computes 4 terms for a cell, of 4 rows and one plane 2.5, of 4 rows and 16
+// Small grids are bound by the launches and a wave's latency, not by instructions:
+// there a thread per cell with its four terms has the shortest chain. On grids
+// of few columns a wave would fill few of its lanes. The call, FP32 / FP64, a
+// thread per cell against a wave per unit:
+//   70 x 70 x 30          17.4 / 18.5 us, 19.0 / 20.1
+//   96 x 96 x 32          18.5 / 20.3 us, 19.4 / 20.6
+//   128 x 128 x 20        18.7 / 20.0 us, 18.8 / 20.4  (five waves per SIMD)
+//   128 x 128 x 44        22.1 / 24.3 us, 20.7 / 22.6
+//   256 x 256 x 40        34.7 / 43.4 us, 26.1 / 32.1
+//   5 x 20 x 30000        37.7 / 46.8 us, 43.5 / 56.6  (100 columns)
+//   12 x 10 x 30000       41.9 / 52.7 us, 39.5 / 52.1
+//   1 x 1 x 100000        16.6 / 17.1 us, 56.1 / 77.4
+// Otherwise narrow grids fold rows into the lanes (1 x 2000 x 300: 21.0 / 23.5 us
+// with one column per wave row, 39.5 / 54.6 with 16). A unit of one row and one
+// plane computes 4 terms for a cell, of 4 rows and one plane 2.5, of 4 rows and 16
 // planes 1.4, but a wave's chain of terms is 4, 10 and 90 long: the larger
 // units are for grids that still fill every SIMD with several waves (256 x
-// 256 x 64: 4 rows, 4 planes). The planes per unit are at most those that the
-// lanes can hold column halos of, 64 / (row groups * rows).
+// 256 x 64: 4 rows, 4 planes), have rows for them (20000 x 1 x 64: 23.0 us with
+// one row, 28.3 with four; 20000 x 3 x 64: 31.4 with four) and whose lanes can hold
+// the column halos: 64 / (row groups * rows) planes per unit.
 inline TvPlan tv_plan(int nx, int ny, int nz, int cus) {
-  TvPlan P;
-  P.lx = nx > 32 ? 6 : (nx > 16 ? 5 : 4);
+  TvPlan P{};
+  if ((long long)nx * ny <= kTvThin || (long long)nx * ny * nz <= (long long)cus * 4 * 64 * kTvCellWaves) {
+    P.blocks = (int)std::min<long long>(((long long)nx * ny * nz + kTvBlock - 1) / kTvBlock, kTvMaxBlocks);
+    return P;
+  }
+  while (P.lx < 6 && nx > 1 << P.lx) ++P.lx;
   const int groups = 64 >> P.lx;
   const long long want = (long long)cus * 4 * kTvWaves;
   P.ux = (int)(((long long)nx + (1 << P.lx) - 1) >> P.lx);
   P.rows = kTvRows;
   P.uy = (int)(((long long)ny + groups * P.rows - 1) / (groups * P.rows));
-  if ((long long)P.ux * P.uy * nz < want) {
+  if (P.lx < 2 || ny <= 2 * groups || (long long)P.ux * P.uy * nz < want) {
     P.rows = 1;
     P.uy = (int)(((long long)ny + groups - 1) / groups);
   }
@@ -119,6 +140,20 @@ __device__ __forceinline__ unsigned tv_row(unsigned j, unsigned ny) {
   j = j == ~0u ? ny - 1 : j;
   j = j >= ny ? j - ny : j;
   return j >= ny ? 0 : j;
+}
+
+// The workgroup's sum of t in a fixed order: wave butterfly, then the waves in order.
+template <typename R>
+__device__ __forceinline__ void tv_partial(const TvArgs<R>& A, double tsum) {
+  __shared__ double red[kTvBlock / 64];
+  tsum = wave_sum(tsum);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = tsum;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double s = 0.0;
+    for (int w = 0; w < kTvBlock / 64; ++w) s += red[w];
+    A.partial[blockIdx.x] = s;
+  }
 }
 
 template <typename R, int K>
@@ -225,16 +260,39 @@ __global__ void __launch_bounds__(kTvBlock) tv_kernel(TvArgs<R> A) {
       for (int s = 0; s < K + 1; ++s) ax[s] = anx[s];
     }
   }
-  // workgroup sum in a fixed order: wave butterfly, then the waves in order
-  tsum = wave_sum(tsum);
-  __shared__ double red[kTvBlock / 64];
-  if (lane == 0) red[wave] = tsum;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    double s = 0.0;
-    for (int w = 0; w < kTvBlock / 64; ++w) s += red[w];
-    A.partial[blockIdx.x] = s;
+  tv_partial(A, tsum);
+}
+
+// A thread per cell with its four terms (P.rows == 0), the same factors and chain.
+template <typename R>
+__global__ void __launch_bounds__(kTvBlock) tv_cell_kernel(TvArgs<R> A) {
+  double tsum = 0.0;
+  const unsigned nx = A.nx, ny = A.ny, nz = A.nz, nxy = (unsigned)A.nxy;   // (small)
+  const long long ng = A.nxy * nz;
+  for (long long p = (long long)blockIdx.x * kTvBlock + threadIdx.x; p < ng; p += (long long)gridDim.x * kTvBlock) {
+    const unsigned k = (unsigned)(p / nxy), c = (unsigned)(p - (long long)k * nxy), j = c / nx, i = c - j * nx;
+    auto term = [&](unsigned ti, unsigned tj, unsigned tk, TvTerm<R>& o) -> R {
+      const R* q = A.alpha + (long long)tk * nxy;
+      const R ap = q[ti + nx * tj];
+      return tv_term(A, ap, q[(ti + 1 < nx ? ti + 1 : 0) + nx * tj], q[ti + nx * (tj + 1 < ny ? tj + 1 : 0)],
+                     tk + 1 < nz ? q[nxy + ti + nx * tj] - ap : R(0), o);
+    };
+    TvTerm<R> o, l;
+    const R t = term(i, j, k, o);
+    R g = -fma_r(o.cz, o.rt, fma_r(o.cx, o.rt, mul_rn(o.cy, o.rt)));
+    term(i > 0 ? i - 1 : nx - 1, j, k, l);
+    g = fma_r(l.cx, l.rt, g);
+    term(i, j > 0 ? j - 1 : ny - 1, k, l);
+    g = fma_r(l.cy, l.rt, g);
+    if (k > 0) {
+      term(i, j, k - 1, l);
+      g = fma_r(l.cz, l.rt, g);
+    }
+    const double v = mul_rn(A.scale, (double)g);
+    A.grad[p] = A.accumulate ? add_rn(A.grad[p], v) : v;
+    tsum += (double)t;
   }
+  tv_partial(A, tsum);
 }
 
 // value = scale * sum of the partials: each thread its own in order, then the
