@@ -389,7 +389,9 @@ void plan(nh_ctx* c, int occ, int block, bool resident_ok = false, bool tb_ok = 
   if (brick_size > 0 && plan_brick(c, brick_size)) return;
   resident_ok = resident_ok && !c->periodic && c->robin == 0 && c->jacobi_k == 0;
   c->jac_tb = false;
-  if (tb_ok && c->jacobi_k > 0 && c->nz <= nh::kJacNZDeep && c->tile_z == 0) {
+  // (the deep kernels have no stamps: a traced context's steps stream)
+  const int tb_nz = c->trace_step > 0 ? nh::kJacNZ : nh::kJacNZDeep;
+  if (tb_ok && c->jacobi_k > 0 && c->nz <= tb_nz && c->tile_z == 0) {
     // the lowest interior tiles that leave every workgroup a CU: their sweeps
     // are the shortest (64x64x16, K = 50: 1.46 us per sweep with tiles of 2
     // rows, 1.70 with 4, 2.45 with 8; 75x50x24: 2.10 with 2, 2.71 with 4, 9.6 in
@@ -640,7 +642,7 @@ template <typename R>
 nh_status launch_step(nh_ctx* c, StepArgs<R>& S, int slot_ev, double* t_kernel) {
   if (c->brick_nt > 0) return queue_brick<R>(c, S, slot_ev);
   if constexpr (sizeof(R) == 4) {
-    if (c->jac_tb && (!S.trace || c->nz > nh::kJacNZ)) {
+    if (c->jac_tb && !S.trace) {
       bool launched = false;
       NH_TRY(queue_step(c, S, slot_ev, &launched));
       (void)t_kernel;

@@ -131,3 +131,18 @@ hip.host_hip_reset()
 assert adjoint(5) == 0                       # the forward is still saved
 assert len(launches(*STEPS)) == 1, launches(*STEPS)
 """)
+
+
+@pytest.mark.parametrize("grid,kernel", [("64, 64, 16", "jacobi_step_kernelILi"), ("40, 20, 24", "11step_kernelI")],
+                         ids=["nz16", "nz24"])
+def test_a_traced_fixed_k_step_runs_a_kernel_that_stamps(run, grid, kernel):
+    """NH_TRACE_STEP prints the phase timings of one step: with more than 16 planes,
+    where the blocked kernel has no stamps, of the streaming kernel."""
+    r = run(f"""
+grid({grid})
+lib.nh_set_jacobi_sweeps(ctx, 6)
+assert forward(3) == 0
+ran = launches(*STEPS, "jacobi_step_kernel")
+assert any({kernel!r} in l for l in ran) and not any("jacobi_deep" in l for l in ran), ran
+""", NH_TRACE_STEP="2", NH_TRACE_RANK="0")
+    assert "[nh trace] step 2" in r.stderr
