@@ -885,28 +885,21 @@ template <typename R>
 nh_status ensure_common(nh_ctx* c, int nsteps) {
   const size_t vb = sizeof(R) * (size_t)c->geom.ng;
   NH_TRY(ensure(c, c->alpha, vb));
-  NH_TRY(ensure(c, c->z, vb));
-  NH_TRY(ensure(c, c->p0, vb));
-  if (c->variant == 0) {
-    NH_TRY(ensure(c, c->p1, vb));
-    NH_TRY(release(c, c->u1));
-    if (c->cheb_m >= 2 && c->jacobi_k == 0) {   // the Chebyshev preconditioner's y buffers
-      NH_TRY(ensure(c, c->vw0, vb));
-      NH_TRY(ensure(c, c->vw1, vb));
-    } else {
-      NH_TRY(release(c, c->vw0));
-      NH_TRY(release(c, c->vw1));
-    }
-    NH_TRY(release(c, c->vs0));
-    NH_TRY(release(c, c->vs1));
-  } else {
-    NH_TRY(release(c, c->p1));
-    NH_TRY(ensure(c, c->u1, vb));
-    NH_TRY(ensure(c, c->vw0, vb));
-    NH_TRY(ensure(c, c->vw1, vb));
-    NH_TRY(ensure(c, c->vs0, vb));
-    NH_TRY(ensure(c, c->vs1, vb));
-  }
+  // the CG vectors of the streaming and resident kernels (bricks have none in memory)
+  const bool mem = c->brick_nt == 0, two = c->variant == 0;
+  const bool cheb = two && c->cheb_m >= 2 && c->jacobi_k == 0;   // the preconditioner's y buffers
+  const struct {
+    Buf& b;
+    bool held;
+  } vecs[] = {{c->z, mem},
+              {c->p0, mem},
+              {c->p1, mem && two},
+              {c->u1, mem && !two},
+              {c->vw0, mem && (!two || cheb)},
+              {c->vw1, mem && (!two || cheb)},
+              {c->vs0, mem && !two},
+              {c->vs1, mem && !two}};
+  for (const auto& v : vecs) NH_TRY(v.held ? ensure(c, v.b, vb) : release(c, v.b));
   if (sizeof(R) == 4 && c->resident)   // three vectors, two banks
     NH_TRY(ensure(c, c->xface, sizeof(float) * 2 * (size_t)c->team * nh::kXfTile));
   else

@@ -4,6 +4,7 @@
 // workspaces, clears) runs on any machine and a test reads what it launched.
 #include <hip/hip_runtime_api.h>
 
+#include <cstdio>
 #include <cstdlib>
 #include <cstring>
 #include <map>
@@ -17,6 +18,10 @@ std::map<const void*, std::string>& names() {
 std::string& launches() {
   static std::string s;
   return s;
+}
+std::map<void*, size_t>& blocks() {
+  static std::map<void*, size_t> m;
+  return m;
 }
 int fail_cooperative = 0;                    // the n-th next cooperative launch fails (0: none)
 struct Config {
@@ -36,6 +41,11 @@ extern "C" {
 
 const char* host_hip_launches() { return launches().c_str(); }
 void host_hip_reset() { launches().clear(); }
+size_t host_hip_bytes() {                    // of device memory held now
+  size_t n = 0;
+  for (const auto& b : blocks()) n += b.second;
+  return n;
+}
 void host_hip_fail_cooperative(int n) { fail_cooperative = n; }
 
 void** __hipRegisterFatBinary(const void*) {
@@ -72,9 +82,12 @@ hipError_t hipLaunchCooperativeKernel(const void* f, dim3, dim3, void** args, un
 
 hipError_t hipMalloc(void** p, size_t n) {
   *p = std::calloc(1, n);
-  return *p ? hipSuccess : hipErrorOutOfMemory;
+  if (!*p) return hipErrorOutOfMemory;
+  blocks()[*p] = n;
+  return hipSuccess;
 }
 hipError_t hipFree(void* p) {
+  blocks().erase(p);
   std::free(p);
   return hipSuccess;
 }

@@ -16,10 +16,12 @@ import ctypes, sys
 hip = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
 lib = ctypes.CDLL(sys.argv[2])
 hip.host_hip_launches.restype = ctypes.c_char_p
+hip.host_hip_bytes.restype = ctypes.c_size_t
 VP, D = ctypes.c_void_p, ctypes.c_double
 lib.nh_create.argtypes = [VP, ctypes.c_int, VP]
 lib.nh_set_grid.argtypes = [VP, ctypes.c_int, ctypes.c_int, ctypes.c_int, D, D, D]
 lib.nh_set_launch.argtypes = [VP, ctypes.c_int, ctypes.c_int, ctypes.c_int]
+lib.nh_set_cg_variant.argtypes = [VP, ctypes.c_int]
 lib.nh_set_jacobi_sweeps.argtypes = [VP, ctypes.c_int]
 lib.nh_set_boundary.argtypes = [VP, ctypes.c_int, D]
 for f in (lib.nh_forward, lib.nh_forward_f64):
@@ -146,3 +148,20 @@ ran = launches(*STEPS, "jacobi_step_kernel")
 assert any({kernel!r} in l for l in ran) and not any("jacobi_deep" in l for l in ran), ran
 """, NH_TRACE_STEP="2", NH_TRACE_RANK="0")
     assert "[nh trace] step 2" in r.stderr
+
+
+@pytest.mark.parametrize("double", [False, True], ids=["f32", "f64"])
+def test_bricks_hold_no_streaming_vectors(run, double):
+    """The brick kernel keeps the CG state in registers: a context's memory is the
+    states, the diffusivity and three banks of halo words of twice a value's size,
+    and shrinks to that when a grid that streamed becomes one of bricks."""
+    run(f"""
+grid(64, 64, 16)
+value = {8 if double else 4}
+assert lib.nh_set_cg_variant(ctx, 1) == 0 and forward(6, {double}) == 0 and launches("11step_kernelI")
+assert hip.host_hip_bytes() > (6 + 1 + 7) * value * cells
+assert lib.nh_set_cg_variant(ctx, 2) == 0 and forward(6, {double}) == 0 and launches("brick_steps_kernel")
+assert hip.host_hip_bytes() < (6 + 1 + 3 * 2) * value * cells + 2 * 64 * 256 + value * columns + 4096, hip.host_hip_bytes()
+assert lib.nh_set_cg_variant(ctx, 0) == 0 and forward(6, {double}) == 0
+assert lib.nh_set_cg_variant(ctx, 2) == 0 and forward(6, {double}) == 0
+""")
