@@ -155,7 +155,7 @@ struct nh_ctx {
   // workspaces
   Buf alpha, qxy, z, p0, p1, u1, vw0, vw1, vs0, vs1, traj, seg, slots, steps, flag;
   Buf tvpart;                                // per-workgroup partial sums of the TV regulariser
-  Buf xface;                                 // resident kernel: compact x-edge columns of u, w/D, s/D
+  Buf xface;                                 // resident kernel: compact x-edge columns of u, w/D
   Buf srcq, srcqt;                           // source gradients: dL/dq^n series, q_t on the device
   double* scratch = nullptr;                 // this device's scratch array (nh_tv_noalloc)
   Buf halo;                                  // brick kernel: tagged halo words
@@ -327,7 +327,12 @@ BrickQueue<double>& brick_queue(nh_ctx* c, double) { return c->bq64; }
 // bricks of 32 x 16 columns 4.9, 192 of 64 x 8 5.2), less the exchange where
 // one brick holds the grid (16x16x8: one workgroup 2.5 us, two 3.6); among
 // equals the widest (coalesced edges: 100x75x30 4.9 us with 64 columns, 5.1
-// with 32).
+// with 32). The times were measured on small grids, and order the shapes; that
+// bricks beat the resident kernel wherever they fit was measured on the large
+// ones, 12 steps against its best tile depth: 160x160x24 7.1 ms, 11.2; 256x128x32
+// (bricks of eight cells a thread on every CU) 7.9, 12.8; 256x256x16 7.7, 12.3;
+// 1000x60x9 7.3, 10.6; 33x500x40 9.4, 13.3. FP64 against streaming: 128x128x32
+// 12.5 ms, some 28 (128x128x40, which does not fit).
 bool plan_brick(nh_ctx* c, int size) {
   if (c->variant != 2 || c->jacobi_k > 0 || c->tile_z > 0 || c->team_max > 0 || c->trace_step > 0) return false;
   double best = 1e30;
@@ -394,7 +399,7 @@ void plan(nh_ctx* c, int occ, int block, bool resident_ok = false, bool tb_ok = 
   if (tb_ok && c->jacobi_k > 0 && c->nz <= tb_nz && c->tile_z == 0) {
     // the lowest interior tiles that leave every workgroup a CU: their sweeps
     // are the shortest (64x64x16, K = 50: 1.46 us per sweep with tiles of 2
-    // rows, 1.70 with 4, 2.45 with 8; 75x50x24: 2.10 with 2, 2.71 with 4, 9.6 in
+    // rows, 1.70 with 4, 2.45 with 8; 75x50x24: 2.0 with 2, 2.71 with 4, 7.1 in
     // the streaming kernel)
     long long cap = c->num_cu;
     if (c->team_max > 0) cap = std::min<long long>(cap, c->team_max);
@@ -900,7 +905,7 @@ nh_status ensure_common(nh_ctx* c, int nsteps) {
               {c->vs0, mem && !two},
               {c->vs1, mem && !two}};
   for (const auto& v : vecs) NH_TRY(v.held ? ensure(c, v.b, vb) : release(c, v.b));
-  if (sizeof(R) == 4 && c->resident)   // three vectors, two banks
+  if (sizeof(R) == 4 && c->resident)   // two vectors, two banks
     NH_TRY(ensure(c, c->xface, sizeof(float) * 2 * (size_t)c->team * nh::kXfTile));
   else
     NH_TRY(release(c, c->xface));

@@ -4,7 +4,7 @@
 //
 // An exchange between workgroups costs 1.5-2 us on this chip, more than a sweep
 // of a small grid, so a step that exchanges after every sweep is bound by it
-// (75x50x24: 7.2 us per sweep with a team reduction each). Here each workgroup
+// (75x50x24 in the streaming kernel: 7.1 us per sweep with a team reduction each). Here each workgroup
 // owns an interior tile of kJacIX x IY columns and computes on the tile widened
 // by kJacS columns on every lateral side (an extended tile of kJacEX x (IY + 6)
 // columns, two threads per column, each with half of the column's cells, their
@@ -40,7 +40,9 @@
 // instructions, 8 cells of ~17 for two waves per SIMD, and one LDS round trip),
 // 3.66 with 24 workgroups of 24 x 8 columns, four neighbours of a cell read
 // through LDS, b and 1/D in LDS, halo words awaited one by one and a reduction
-// per step. 75x50x24: 2.1 us, 13.7 with a team reduction per sweep.
+// per step. 75x50x24: 2.0 us, 7.1 in the streaming kernel, 13.7 there before its
+// team reduction became one exchange (each with the steps' set-up; the sweeps
+// alone, from K = 75 to 150: 1.8, 6.7 and 12.5 us).
 #pragma once
 
 #include "nh_kernels.hpp"

@@ -20,13 +20,16 @@
 // accesses, the team reduction needs no L2 write-back or invalidation. The
 // arithmetic is the same as the streaming kernel's single-reduction form.
 //
-// On 256 x 256 x 64 (256 tiles of 32 planes) an iteration of about 18 us is
-// bound by the sweep's vector instructions (49 per cell, 6 of them reciprocals
-// at a quarter of the rate: 7.1 us of some 10) and by the reduction's latency
-// (6 us). 48 steps with a step of 10 s took 116.3 ms with three
-// vectors published and loaded, 93.3 ms with A u / D alone, and 84.7 ms with
-// the z faces' reciprocal kept from plane to plane, no branch between the
-// planes of a group and the ring read a group ahead.
+// On 256 x 256 x 64 (256 tiles of 32 planes) an iteration of about 18 us is 0.5 us
+// of register updates, 0.9 of waiting for and advancing the ring, 10 to 11 of
+// sweep, bound by its vector instructions (49 per cell, 6 of them reciprocals
+// at a quarter of the rate: 7.1 us if nothing else took time), and 6 us of
+// reduction (2.7 us alone: the rest is the workgroups' skew and the halo loads
+// that travel inside it). 48 steps with a step of 10 s took 118.7 ms with three
+// vectors published and loaded and a master's reduction, 116.3 with the present
+// reduction, 93.3 with A u / D alone exchanged, and 84.7 with the z faces'
+// reciprocal kept from plane to plane, no branch between the planes of a group and
+// the ring read a group ahead.
 #pragma once
 
 #include "nh_kernels.hpp"
@@ -492,7 +495,8 @@ __device__ __forceinline__ StepResult resident_step(const StepArgs<float>& S, co
   }
 
   // rings 1 and 2 receive only in-grid values by direct loads: their other
-  // slots stay zero (ring 0 is fully rewritten by the set-up's fill)
+  // slots stay zero. (Ring 0 is written by the set-up's fill on the tile's planes,
+  // zeros outside the grid among them; its slots past them hold what LDS held.)
   for (int e = tid0; e < 2 * kResTZ * kRing; e += kResBlock) lring[kResTZ * kRing + e] = 0.f;
 
   float pr[TZ], ur[TZ], wr[TZ], sr[TZ];
@@ -724,7 +728,9 @@ __device__ __forceinline__ StepResult resident_step(const StepArgs<float>& S, co
       __builtin_amdgcn_s_waitcnt(0);        // the ring loads have reached LDS
       __syncthreads();
       // the ring's new s and u, in place
-      // (every slot: slots past the tile's planes and outside the grid hold zeros)
+      // (every slot: those outside the grid hold zeros; so do w's and s's past the
+      // tile's planes, u's there hold anything, NaN too, and are read only by
+      // the planes past the tile's end, whose A u the sweep sets to zero)
 #pragma unroll
       for (int e0 = 0; e0 < kResTZ * kRing; e0 += kResBlock) {
         const int e = e0 + tid_l;
@@ -908,8 +914,8 @@ __global__ void __launch_bounds__(kResBlock, 1) resident_step_kernel(StepArgs<fl
 }
 
 // Every tile of kResTZ planes: none ends inside a group of planes, whose masks
-// (4 of 53 vector instructions per cell) drop out. 87.1 ms against 88.6 ms with
-// the general instance, on 256 x 256 x 64.
+// (4 of 53 vector instructions per cell) drop out. Against the general instance:
+// 12 steps of 130 x 20 x 64 22.5 ms, 24.0; 48 of 256 x 256 x 64 95.2, 95.8.
 template <int TXC>
 __global__ void __launch_bounds__(kResBlock, 1) resident_full_kernel(StepArgs<float> S) {
   extern __shared__ __align__(16) unsigned char dsm[];
